@@ -887,30 +887,90 @@ __global__ void norms64(int K, int PL, const R *D, double *nrm) {
 
 // ------------------------------------------------------------- grid plan
 struct Plan {
-  int W1, W2, tile1, tile2, mmax, nt;
+  int W1, W2, tile1, tile2, mmax;
 };
 
-template <class R, int NT>
-int capacity(DeviceState *ds, int *cap) {
-  int nb = 0;
-  HIPCK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void *>(lgcd_rounds<R, NT>), NT, 0));
-  *cap = nb * ds->cus;
-  return DCDL_OK;
-}
-
-// Workgroup sizes the round kernel is built for.
+// Values of the `threads` option.
 bool valid_nt(int nt) { return nt == 64 || nt == 128 || nt == 192 || nt == 256 || nt == 512 || nt == 1024; }
+
+// Workers a CU holds at `nt` threads each.  The worker grids the library
+// chooses follow from it, so it is a constant of the option and the type, not
+// of what a build of the kernel happens to occupy.
+int workers_per_cu(int nt, bool f32) {
+  if (nt <= 192) return 4;
+  if (nt == 256) return f32 ? 4 : 3;
+  return nt == 512 && f32 ? 2 : 1;
+}
 
 template <class R>
 int capacity_nt(DeviceState *ds, int nt, int *cap) {
-  switch (nt) {
-    case 64: return capacity<R, 64>(ds, cap);
-    case 128: return capacity<R, 128>(ds, cap);
-    case 192: return capacity<R, 192>(ds, cap);
-    case 512: return capacity<R, 512>(ds, cap);
-    case 1024: return capacity<R, 1024>(ds, cap);
-    default: return capacity<R, 256>(ds, cap);
+  *cap = workers_per_cu(nt, sizeof(R) == 4) * ds->cus;
+  return DCDL_OK;
+}
+
+// How a launch's workers are put on workgroups: threads per workgroup, and
+// per instance the team of G1 x G2 workers a workgroup runs.
+struct Teams {
+  int G1 = 1, G2 = 1, TW1 = 1, TW2 = 1;
+  int count() const { return TW1 * TW2; }
+  bool set(int W1, int W2, int g1, int g2) {
+    G1 = std::min(g1, W1);
+    G2 = std::min(g2, W2);
+    TW1 = (W1 + G1 - 1) / G1;
+    TW2 = (W2 + G2 - 1) / G2;
+    return G1 * G2 <= kTeamMax && (std::min(W1, G1 + 2)) * (std::min(W2, G2 + 2)) <= kUpdMax;
   }
+};
+
+// Teams of about `per` workers for a W1 x W2 worker grid: the shape with the
+// fewest workgroups, and of those the one of fewest workers per team.
+Teams teams_of(int W1, int W2, int per) {
+  Teams best, t;
+  best.set(W1, W2, 1, 1);
+  for (int a = 1; a <= per && a <= W1; ++a)
+    for (int b = 1; a * b <= per && b <= W2; ++b) {
+      if (!t.set(W1, W2, a, b)) continue;
+      if (t.count() < best.count() || (t.count() == best.count() && t.G1 * t.G2 < best.G1 * best.G2)) best = t;
+    }
+  return best;
+}
+
+// Lanes one patch keeps busy.
+int patch_lanes_of(const Geom &g, int vec) {
+  const LaneMap lm = lane_map(g.KS / vec);
+  const long long n = (long long)g.U1 * g.U2 << lm.sh;
+  return (int)std::min<long long>(n, 1 << 20);
+}
+
+// The teams and the workgroup size of a launch over `grids` (W1, W2) of
+// instances of patches of `lanes` lanes.  Workgroups of 1024 threads, one per
+// CU, run as few workers each as the CUs allow: more workers per team than that
+// leave CUs idle (150x203 image, 48 workers, us per round: 13.2 with one per
+// team, 15.2 with two, 19.6 with four), and four workers in a team of 1024
+// threads beat four workgroups of 256 (1024^2 image: 40.6 against 42.3 us).
+// Where a patch keeps no more than five waves busy (signals of few atoms), or
+// teams of four workers would not fit (uneven or many instances, whose largest
+// one would set the time), one worker per workgroup of 256
+// threads, four per CU (FP64 signal, 39 workers: 9.9 us against 10.1 with
+// 1024 threads, 10.6 and 11.1 with two and four workers per team).
+int plan_teams(const std::vector<std::pair<int, int>> &grids, int lanes, int cus, std::vector<Teams> *out) {
+  const int n = (int)grids.size();
+  out->resize(n);
+  long long workers = 0;
+  for (int i = 0; i < n; ++i) {
+    (*out)[i].set(grids[i].first, grids[i].second, 1, 1);
+    workers += (*out)[i].count();
+  }
+  if (lanes <= 320 && workers <= 4ll * cus) return 256;
+  for (int per = 1; per <= 4; ++per) {
+    long long wgs = 0;
+    for (int i = 0; i < n; ++i) wgs += teams_of(grids[i].first, grids[i].second, per).count();
+    if (wgs <= cus) {
+      for (int i = 0; i < n; ++i) (*out)[i] = teams_of(grids[i].first, grids[i].second, per);
+      return 1024;
+    }
+  }
+  return 256;
 }
 
 int plan_grid(const Geom &g, int ndim, const dcdl_csc_opts *o, int cap, Plan *p) {
@@ -970,20 +1030,26 @@ int plan_grid(const Geom &g, int ndim, const dcdl_csc_opts *o, int cap, Plan *p)
   return DCDL_OK;
 }
 
+// One cooperative launch of the round kernel: nwg workgroups of nt threads
+// (256 or 1024) over instances of atom stride KS.  ext: the
+// random rule or several visits per round.
 template <class R>
-int launch_rounds(hipStream_t stream, int nt, Inst<R> *d_inst, int *d_wg, int nwg, long long timeout_ticks) {
+int launch_rounds(hipStream_t stream, int nt, bool ext, int KS, Inst<R> *d_inst, int *d_wg, int nwg,
+                  long long timeout_ticks) {
   void *args[] = {&d_inst, &d_wg, &timeout_ticks};
-  const void *fn;
-  switch (nt) {
-    case 64: fn = reinterpret_cast<const void *>(lgcd_rounds<R, 64>); break;
-    case 192: fn = reinterpret_cast<const void *>(lgcd_rounds<R, 192>); break;
-    case 128: fn = reinterpret_cast<const void *>(lgcd_rounds<R, 128>); break;
-    case 512: fn = reinterpret_cast<const void *>(lgcd_rounds<R, 512>); break;
-    case 1024: fn = reinterpret_cast<const void *>(lgcd_rounds<R, 1024>); break;
-    default: fn = reinterpret_cast<const void *>(lgcd_rounds<R, 256>); break;
-  }
+  const int ng = lane_map(KS / Vec<R>::N).ng;
+  const void *fn = nt == 1024 ? rounds_kernel<R, 1024>(ng, ext) : rounds_kernel<R, 256>(ng, ext);
   HIPCK(hipLaunchCooperativeKernel(fn, dim3(nwg), dim3(nt), args, 0, stream));
   return DCDL_OK;
+}
+
+template <class R>
+void set_teams(Inst<R> *I, const Teams &t) {
+  I->G1 = t.G1;
+  I->G2 = t.G2;
+  I->TW1 = t.TW1;
+  I->TW2 = t.TW2;
+  I->lane_sh = lane_map(I->KS / Vec<R>::N).sh;
 }
 
 double now_s() {
@@ -999,26 +1065,16 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
   g.KS = atom_stride(g.K, (int)sizeof(R));
   const long long HW = (long long)g.H * g.W, nz = HW * g.KS;
   const long long nA = (long long)g.K * g.U1 * g.U2 * g.KS;
-  int nt = valid_nt(o->threads) ? o->threads : 256;
+  const int nt = valid_nt(o->threads) ? o->threads : 256;
   int cap = 0, rc = capacity_nt<R>(ds, nt, &cap);
   if (rc) return rc;
   Plan pl;
   if ((rc = plan_grid(g, ndim, o, cap, &pl))) return rc;
   const int nW = pl.W1 * pl.W2;
-  if (o->threads == 0 && ndim == 2) {
-    // a grid that leaves workgroup slots of the CUs empty (one or two workers
-    // per CU) gives each worker the threads of those slots: its scans and
-    // patches then run on 4x or 2x the waves (the 16x16 grid of a 1024^2
-    // image: 2.3x faster rounds).  Signals keep 256 threads, faster there.
-    for (int big : {1024, 512}) {
-      int capb = 0;
-      if ((rc = capacity_nt<R>(ds, big, &capb))) return rc;
-      if (nW <= capb) {
-        nt = big;
-        break;
-      }
-    }
-  }
+  std::vector<Teams> teams;
+  const int wg_nt = plan_teams({{pl.W1, pl.W2}}, patch_lanes_of(g, Vec<R>::N), ds->cus, &teams);
+  const int nwg = teams[0].count();
+  const bool ext = o->strategy == DCDL_SELECT_RANDOM || o->inner > 1;
 
   R *beta, *zpm, *A, *dtd, *inv_n, *score;
   uint32_t *meta;
@@ -1035,7 +1091,7 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
   WS("dtd", sizeof(R) * (size_t)g.K * g.K * g.U1 * g.U2, dtd);
   WS("inv_n", sizeof(R) * g.KS, inv_n);
   WS("nrm64", sizeof(double) * g.K, nrm64);
-  WS("cand", sizeof(unsigned long long) * 2 * nW, cand);
+  WS("cand", sizeof(unsigned long long) * kCandWords * nW, cand);
   WS("prog", sizeof(int) * nW, prog);
   WS("wg", sizeof(int) * nW, wg);
   WS("ctl", sizeof(Ctl) + sizeof(int) * 2 * kRing, ctl);
@@ -1105,6 +1161,7 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
   hi.prog = prog;
   hi.ctl = ctl;
   hi.ring = reinterpret_cast<int *>(ctl + 1);
+  set_teams(&hi, teams[0]);
   HIPCK(hipMemsetAsync(wg, 0, sizeof(int) * nW, stream));
 
   const double kkt_target = o->kkt_target > 0 ? o->kkt_target : 1e-4;
@@ -1168,10 +1225,10 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
     HIPCK(hipMemcpyAsync(d_inst, &hi, sizeof(hi), hipMemcpyHostToDevice, stream));
     HIPCK(hipMemsetAsync(prog, 0, sizeof(int) * nW, stream));
     // all-ones tags carry a round number no launch reaches
-    HIPCK(hipMemsetAsync(cand, 0xff, sizeof(unsigned long long) * 2 * nW, stream));
+    HIPCK(hipMemsetAsync(cand, 0xff, sizeof(unsigned long long) * kCandWords * nW, stream));
     HIPCK(hipMemsetAsync(ctl, 0, sizeof(Ctl) + sizeof(int) * 2 * kRing, stream));
     HIPCK(hipEventRecord(ev1, stream));
-    if ((rc = launch_rounds<R>(stream, nt, d_inst, wg, nW, timeout_ticks))) return rc;
+    if ((rc = launch_rounds<R>(stream, wg_nt, ext, g.KS, d_inst, wg, nwg, timeout_ticks))) return rc;
     HIPCK(hipEventRecord(ev2, stream));
     Ctl hc;
     HIPCK(hipMemcpyAsync(&hc, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
@@ -1387,7 +1444,7 @@ size_t csc_scratch_need(const Geom &g_user, const dcdl_csc_opts *o) {
   const size_t HW = (size_t)g.H * g.W, nz = HW * g.KS, nA = (size_t)g.K * g.U1 * g.U2 * g.KS;
   const size_t nW = 8192;
   size_t need = 2 * r(es * nz) + r(es * HW) + r(4 * HW) + r(es * nA) + r(es * g.K * g.K * g.U1 * g.U2) +
-                r(es * g.KS) + r(8 * (size_t)g.K) + r(16 * nW) + 2 * r(4 * nW) +
+                r(es * g.KS) + r(8 * (size_t)g.K) + r(8 * kCandWords * nW) + 2 * r(4 * nW) +
                 r(sizeof(Ctl) + sizeof(int) * 2 * kRing) + r(std::max(sizeof(Inst<float>), sizeof(Inst<double>)));
   need += r(8 * (size_t)g.K * g.P * g.L1 * g.L2) + r(8 * (size_t)g.P * g.T1 * g.T2) + r(64);
   Geom gi;

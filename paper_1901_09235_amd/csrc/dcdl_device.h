@@ -9,8 +9,9 @@
 //   score   : per position, the best move score over its K atoms (Alg. 1's
 //             selection key); read by neighbouring workers, so it is accessed
 //             with coherent atomics.
-//   meta    : per position, the atom of that best move (low 16 bits) and the
-//             number of non-zero atoms (high 16 bits); private to the owner.
+//   meta    : per position, the number of non-zero atoms (high 16 bits);
+//             private to the owner.  The atom of a best move is not kept: the
+//             worker that selects a position finds it from beta and z.
 //   A       : apply table A[k0][d1][d2][k] = DtD[k][k0][d1][d2] (k padded to KS):
 //             the row of eq. beta_update for an update of atom k0, indexed by
 //             the offset d = w - w0 + L - 1 of the patched position w.
@@ -81,6 +82,10 @@ template <class R> struct Inst {
   int K, KS, L1, L2, U1, U2;
   int H, W;
   int W1, W2, tile1, tile2, mmax, wg_base;
+  // workgroups ("teams") of this instance: TW1 x TW2, each running a block of
+  // G1 x G2 workers (fewer at the far edges)
+  int G1, G2, TW1, TW2;
+  int lane_sh;  // lane_map(KS / vector).sh
   int inner;  // sub-domain visits per round (at most Mw); 0 -> 1
   int positive, certify, soft_lock;
   int strategy;  // dcdl_select: 0 LGCD, 1 greedy, 2 cyclic (both through tile1/tile2), 3 random
@@ -92,8 +97,8 @@ template <class R> struct Inst {
   R *score;        // shared: coherent accesses only
   uint32_t *meta;  // private to the owning worker
   const R *A, *inv_n;
-  unsigned long long *cand;  // 2 words per worker
-  int *prog;
+  unsigned long long *cand;  // kCandWords words per worker
+  int *prog;                 // one word per team
   Ctl *ctl;
   int *ring;  // kRing 64-bit slots: completions (low word) and quiet workers (high word) of a round
   // optional, 2 per worker: visits so far and the quiet count, loaded at the
@@ -159,8 +164,22 @@ __device__ __forceinline__ unsigned long long sm64_draw(unsigned long long seed,
 __device__ __forceinline__ int part_start(int j, int N, int Wn) {
   return (int)(((long long)j * N) / Wn);
 }
+// part_start in 32 bits where its products fit.
+__device__ __forceinline__ int part_start_fast(int j, int N, int Wn) {
+  if (((unsigned long long)(unsigned)N * (unsigned)Wn) >> 32) return part_start(j, N, Wn);
+  return (int)((unsigned)j * (unsigned)N / (unsigned)Wn);
+}
 __device__ __forceinline__ int part_owner(int x, int N, int Wn) {
   return (int)((((long long)x + 1) * Wn - 1) / N);
+}
+
+// n / d for 0 <= n < 2^22 and d >= 1, in a few instructions.
+__device__ __forceinline__ int div_small(int n, int d) {
+  int q = (int)((float)n * __builtin_amdgcn_rcpf((float)d));
+  const int rest = n - q * d;
+  if (rest < 0) --q;
+  if (rest >= d) ++q;
+  return q;
 }
 
 // ------------------------------------------------------------ synchronisation
@@ -209,14 +228,15 @@ __device__ __forceinline__ void score_st(float *p, float v) {
 __device__ __forceinline__ void score_st(double *p, double v) {
   st_shared_u64(reinterpret_cast<unsigned long long *>(p), (unsigned long long)__double_as_longlong(v));
 }
-__device__ __forceinline__ uint32_t meta_pack(int argk, int nzc) { return (uint32_t)argk | ((uint32_t)nzc << 16); }
-__device__ __forceinline__ int meta_argk(uint32_t m) { return (int)(m & 0xffffu); }
+__device__ __forceinline__ uint32_t meta_pack(int nzc) { return (uint32_t)nzc << 16; }
 __device__ __forceinline__ int meta_nzc(uint32_t m) { return (int)(m >> 16); }
 
-// A candidate is two 64-bit words: the delta (word 1) and a tag word (word 0)
-// holding the round (22 bits), the atom (10 bits) and the position (32 bits;
-// all ones for "no accepted candidate").  Word 1 is stored and completed
-// before word 0.
+// A candidate is a tag word (word 0) holding the round (22 bits), the atom (10
+// bits) and the position (32 bits; all ones for "no accepted candidate"), and
+// the bits of its delta, 32 per word (word 1, in FP64 also word 2) beside the
+// round in the high half.  A reader polls the words together until each
+// carries its round, so no store waits for another.
+constexpr int kCandWords = 4;  // words per worker (the last one is padding)
 constexpr unsigned kNoPos = 0xffffffffu;
 constexpr int kRoundBits = 22;
 __device__ __forceinline__ unsigned long long cand_tag(int r, int k0, unsigned pos) {
@@ -238,264 +258,385 @@ template <> __device__ __forceinline__ double bits_delta<double>(unsigned long l
   return __longlong_as_double((long long)v);
 }
 
-// Progress counters of the workers in `nbr` must reach `target`.  Returns
-// false after `timeout_ticks` of the 100 MHz clock.
-__device__ __forceinline__ bool wait_progress(const int *prog, const int *sh_nbr, int nn, int self, int target,
-                                              long long timeout_ticks, int *sh_ok) {
-  // lanes 0..nn-1 of the first wave each watch one neighbour, so the polls of
-  // all neighbours are in flight together
-  const int q = threadIdx.x;
-  if (q < nn) {
-    int ok = 1;
-    const int n = sh_nbr[q];
-    if (n != self) {
-      const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-      while (ld_shared_i32(prog + n) < target) {
-        __builtin_amdgcn_s_sleep(1);
-        if ((long long)(__builtin_amdgcn_s_memrealtime() - t0) > timeout_ticks) {
-          ok = 0;
-          break;
-        }
-      }
-    }
-    sh_ok[q] = ok;
-  }
-  __syncthreads();
-  int ok = 1;
-  for (int k = 0; k < nn; ++k) ok &= sh_ok[k];
-  return ok != 0;
-}
-
-// ------------------------------------------------------------ block reductions
-
-// Largest (score, -pos): larger score wins, equal scores go to the lower pos.
-template <class R, int NT>
-__device__ __forceinline__ void block_argmax(R &s, int &pos, R *sh_s, int *sh_p) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    R os = __shfl_xor(s, off, 64);
-    int op = __shfl_xor(pos, off, 64);
-    if (os > s || (os == s && op < pos)) {
-      s = os;
-      pos = op;
-    }
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-    sh_s[wave] = s;
-    sh_p[wave] = pos;
-  }
-  __syncthreads();
-  s = sh_s[0];
-  pos = sh_p[0];
-#pragma unroll
-  for (int q = 1; q < NT / 64; ++q) {
-    R os = sh_s[q];
-    int op = sh_p[q];
-    if (os > s || (os == s && op < pos)) {
-      s = os;
-      pos = op;
-    }
-  }
-  __syncthreads();
-}
-
-template <int NT>
-__device__ __forceinline__ int block_or(int v, int *sh) {
-  v = __any(v) ? 1 : 0;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) sh[wave] = v;
-  __syncthreads();
-  int r = 0;
-#pragma unroll
-  for (int q = 0; q < NT / 64; ++q) r |= sh[q];
-  __syncthreads();
-  return r;
-}
-
 // ------------------------------------------------------------- the round kernel
 
-// Items (position, atom-group pair) one LDS block of a patch holds: 24 KB of
-// best-move staging for FP32 and 20 KB for FP64, so that four FP32 or three
-// FP64 workers share a CU.
-template <class R> struct PatchBuf {
-  static constexpr int N = sizeof(R) == 4 ? 4096 : 2048;
-};
+// Words of the LDS bitmask that marks the positions of a team's region holding
+// a non-zero coordinate (regions of up to 32 * kNzWords positions keep one).
+constexpr int kNzWords = 2048;
 
-// Words of the LDS bitmask that marks the positions of S_w holding a non-zero
-// coordinate (workers of up to 32 * kNzWords positions keep one).
-constexpr int kNzWords = 1024;
+// Workers one team runs at most, and updates that can touch its region (its
+// own workers' and those of the ring of workers around them).
+constexpr int kTeamMax = 16, kUpdMax = 32;
 
 // Rows and columns of one patch block whose cover masks (the updates whose
 // patch covers that row or column) are tabulated in LDS.
 constexpr int kMaskRows = 128, kMaskCols = 512;
 
-template <class R, int NT> struct PatchCtx {
-  R *sh_ps;
-  uint16_t *sh_pk;
-  uint32_t *rowm, *colm;  // cover masks of a block's rows and columns
-  const R *sh_inv_n;
-  uint32_t *nzb;    // bit (h - a1) * ext2 + (w - a2) set when position (h, w) of S_w has a non-zero;
-                    // null for larger workers, whose patches read z everywhere
-  int G;            // 16-byte atom groups per position
-  int a1, a2, ext2;  // origin and width of S_w
+// How the lanes of a wave share a position's atoms: 2^sh neighbouring lanes
+// per position, each with up to ng of its 16-byte atom groups (group
+// lane + i 2^sh), so that the lanes of a position read 16 2^sh contiguous
+// bytes per load.  ng = 0: more groups than 3 per lane of a whole wave.
+struct LaneMap {
+  int sh, ng;
 };
-
-__device__ __forceinline__ void nzb_put(uint32_t *nzb, int t, bool on) {
-  if (on)
-    nzb[t >> 5] |= 1u << (t & 31);
-  else
-    nzb[t >> 5] &= ~(1u << (t & 31));
+__host__ __device__ inline LaneMap lane_map(int G) {
+  LaneMap best{6, 0};
+  int slots = 1 << 30;
+  for (int ng = 1; ng <= 3; ++ng) {
+    int sh = 0;
+    while ((ng << sh) < G) ++sh;
+    if (sh <= 6 && (ng << sh) <= slots) {  // fewest idle slots; on a tie the more groups per lane
+      slots = ng << sh;
+      best = LaneMap{sh, ng};
+    }
+  }
+  return best;
 }
 
+// 16-byte vectors and pointers known to be global (pointers read from a
+// struct are generic to the compiler, whose flat accesses wait on LDS too).
+template <class R> struct NVec;
+template <> struct NVec<float> {
+  typedef float T __attribute__((ext_vector_type(4)));
+};
+template <> struct NVec<double> {
+  typedef double T __attribute__((ext_vector_type(2)));
+};
+template <class T> using GPtr = __attribute__((address_space(1))) T *;
+template <class T> __device__ __forceinline__ GPtr<T> as_global(T *p) { return (GPtr<T>)p; }
+
+template <class R> struct PatchCtx {
+  GPtr<R> beta;
+  GPtr<const R> z, A;
+  GPtr<R> score;
+  R *ls;                  // LDS copy of the region's scores, or null
+  uint32_t *rowm, *colm;  // cover masks of a block's rows and columns
+  const R *inv_n;
+  uint32_t *nzb;     // bit (h - a1) * ext2 + (w - a2) set when position (h, w) of the region has a
+                     // non-zero; null for larger regions, whose patches read z everywhere
+  R lam, nlam, tolc;  // lambda; -lambda (-infinity when positive); tol (0 without certify)
+  int W, U2, KS, G;  // G: 16-byte atom groups per position
+  int sh;            // lane_map(G).sh
+  int a1, a2, ext2;  // origin and width of the region
+};
+
 // An accepted update as the apply phase uses it: atom k0 at (ch, cw0), change
-// delta, and the rows [r1, r2) x columns [c1, c2) of this worker's region it
+// delta, and the rows [r1, r2) x columns [c1, c2) of this team's region it
 // patches.
 template <class R> struct UCand {
   int k0, ch, cw0, r1, r2, c1, c2;
   int aoff;  // element offset in A of (row 0, column 0) for this update: ((k0 U1 - ch + L1 - 1) U2 - cw0 + L2 - 1) KS
   R delta;
+  unsigned ov;  // earlier updates of the list whose patches overlap this one's
 };
 
-// Applies every update of `uc` to this worker's region in one pass over the
-// bounding box [R1, R2) x [C1, C2) of their patches: each position reads beta
-// once, subtracts the contributions of the updates whose patch covers it
-// (eq. beta_update; the updated coordinate of each update keeps its value from
-// before that update), writes beta once and recomputes its best-move cache
-// once.  Positions no update covers are left untouched.  The sum runs over
-// the updates in increasing worker order, as applying them one after another
-// would.  Every thread of the workgroup takes part.
-//
-// The box is cut into blocks of at most LBUF items (a position and a pair of
-// its atom groups), each block with LDS tables of the updates covering its
-// rows and its columns.  A thread runs one item per pass with all its reads
-// in flight before any is used: beta, the DtD row and, where the worker's LDS
-// bitmask marks a non-zero coordinate, z.  The items' best moves meet in LDS,
-// and a last pass reduces them per position into the score cache and the
-// atom half of meta.
-
-// n / d for 0 <= n < 8192 and 1 <= d <= 8192, with m = rcp_of(d): a
-// multiply-high by floor((2^32 - 1) / d) + 1, exact in that range (checked
-// over all of it); d = 1, whose reciprocal does not fit 32 bits, is passed through.
-__device__ __forceinline__ unsigned rcp_of(int d) { return d > 1 ? 0xffffffffu / (unsigned)d + 1u : 0u; }
-__device__ __forceinline__ int div_rcp(int n, int d, unsigned m) { return d > 1 ? (int)__umulhi((unsigned)n, m) : n; }
-
-// A patch item is a position and a pair of its 16-byte atom groups (2 q2 and,
-// if it exists, 2 q2 + 1): the row, column, cover and address work of an item
-// serves eight FP32 (four FP64) atoms, and its six vector reads are in flight
-// together.
-template <class R> struct PItem {
-  typename Vec<R>::T b0, b1, a0, a1, z0, z1;
-  int q2, rr, cc;
-  unsigned m;  // updates covering the item's position, the first one's DtD row in a0/a1
-  bool two;    // the second group exists (an odd group count leaves the last pair half)
-};
-
-// Item `it` of a block of rows [rr0, ...) x columns [cc0, cc0 + ng / G2): its
-// row, column and group pair from two multiply-high divisions (div_rcp with
-// the block's reciprocals mng of ng and mg of G2), its cover mask from the
-// block's row and column tables, then its memory reads.
-template <class R, int NT>
-__device__ __forceinline__ void pitem_load(const Inst<R> &I, const PatchCtx<R, NT> &P, const UCand<R> *uc, int it,
-                                           int nit, int rr0, int cc0, int ng, int G2, unsigned mng, unsigned mg,
-                                           int rowstride, PItem<R> &x) {
-  typedef typename Vec<R>::T V;
-  constexpr int VE = Vec<R>::N;
-  x.m = 0;
-  if (it >= nit) return;
-  const int tr = div_rcp(it, ng, mng);
-  const int rem = it - tr * ng;
-  const int pl = div_rcp(rem, G2, mg);
-  x.q2 = rem - pl * G2;
-  x.rr = rr0 + tr;
-  x.cc = cc0 + pl;
-  x.m = P.rowm[tr] & P.colm[pl];
-  if (!x.m) return;
-  x.two = 2 * x.q2 + 1 < P.G;
-  const long long e = ((long long)x.rr * I.W + x.cc) * I.KS + 2 * x.q2 * VE;
-  const long long ea = uc[__ffs(x.m) - 1].aoff + x.rr * rowstride + x.cc * I.KS + 2 * x.q2 * VE;
-  x.b0 = *reinterpret_cast<const V *>(I.beta + e);
-  x.b1 = x.two ? *reinterpret_cast<const V *>(I.beta + e + VE) : Vec<R>::zero();
-  x.a0 = *reinterpret_cast<const V *>(I.A + ea);
-  x.a1 = x.two ? *reinterpret_cast<const V *>(I.A + ea + VE) : Vec<R>::zero();
-  bool nz = true;
-  if (P.nzb) {
-    const int lt = (x.rr - P.a1) * P.ext2 + (x.cc - P.a2);
-    nz = (P.nzb[lt >> 5] >> (lt & 31)) & 1u;
-  }
-  x.z0 = nz ? *reinterpret_cast<const V *>(I.z + e) : Vec<R>::zero();
-  x.z1 = nz && x.two ? *reinterpret_cast<const V *>(I.z + e + VE) : Vec<R>::zero();
+// The lane's value moved by a DPP control within rows of 16 lanes.
+template <int CTRL> __device__ __forceinline__ float dpp_mov(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+template <int CTRL> __device__ __forceinline__ double dpp_mov(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
 }
 
-template <class R, int NT>
-__device__ __forceinline__ void pitem_apply(const Inst<R> &I, const PatchCtx<R, NT> &P, const UCand<R> *uc, int it,
-                                            int rowstride, PItem<R> &x) {
-  typedef typename Vec<R>::T V;
+// Maximum over the aligned groups of 2^sh lanes, in every lane of a group.
+template <class R> __device__ __forceinline__ R lanes_max(R v, int sh) {
+  if (sh > 0) v = fmax(v, dpp_mov<0xB1>(v));   // quad_perm 1 0 3 2
+  if (sh > 1) v = fmax(v, dpp_mov<0x4E>(v));   // quad_perm 2 3 0 1
+  if (sh > 2) v = fmax(v, dpp_mov<0x141>(v));  // row_half_mirror: the other quad of 8 lanes
+  if (sh > 3) v = fmax(v, dpp_mov<0x140>(v));  // row_mirror: the other 8 of 16 lanes
+  if (sh > 4) v = fmax(v, __shfl_xor(v, 16, 64));
+  if (sh > 5) v = fmax(v, __shfl_xor(v, 32, 64));
+  return v;
+}
+
+// b minus b clipped to [nlam, lam]: ST(b, lambda) for nlam = -lambda and its
+// one-sided form for nlam = -infinity, with st_target's values (b - lam,
+// b + lam or an exact 0).
+__device__ __forceinline__ float shrink(float b, float nlam, float lam) {
+  return b - __builtin_amdgcn_fmed3f(b, nlam, lam);
+}
+__device__ __forceinline__ double shrink(double b, double nlam, double lam) { return b - fmin(fmax(b, nlam), lam); }
+
+__device__ __forceinline__ float fma_neg(float b, float a, float d) { return __builtin_fmaf(-a, d, b); }
+__device__ __forceinline__ double fma_neg(double b, double a, double d) { return __builtin_fma(-a, d, b); }
+
+// v, negated where s is negative.
+__device__ __forceinline__ float with_sign(float v, float s) {
+  return __uint_as_float(__float_as_uint(v) ^ (__float_as_uint(s) & 0x80000000u));
+}
+__device__ __forceinline__ double with_sign(double v, double s) {
+  return __hiloint2double(__double2hiint(v) ^ (__double2hiint(s) & (int)0x80000000), __double2loint(v));
+}
+
+// Best move score over a lane's NG groups (the scores of st_target and
+// move_score; a NaN beta scores nothing).  Where no position of the wave
+// holds a non-zero, the short form |ST(b)| / n.
+template <class R, int NG>
+__device__ __forceinline__ R lane_best(const typename NVec<R>::T *b, const typename NVec<R>::T *z,
+                                       const typename NVec<R>::T *inv, bool nz, R nlam, R lam, R tolc) {
+#pragma clang fp contract(off)
   constexpr int VE = Vec<R>::N;
-  if (!x.m) return;
-  V b0 = x.b0, b1 = x.b1;
-  unsigned m = x.m;
-  bool first = true;
-  while (m) {
-    const int c = __ffs(m) - 1;
-    m &= m - 1;
-    const UCand<R> &u = uc[c];
-    V av0 = x.a0, av1 = x.a1;
-    if (!first) {
-      const long long ea = u.aoff + x.rr * rowstride + x.cc * I.KS + 2 * x.q2 * VE;
-      av0 = *reinterpret_cast<const V *>(I.A + ea);
-      av1 = x.two ? *reinterpret_cast<const V *>(I.A + ea + VE) : Vec<R>::zero();
-    }
-    first = false;
-    const V bold0 = b0, bold1 = b1;
-    b0 = Vec<R>::fma_neg(b0, av0, u.delta);
-    b1 = Vec<R>::fma_neg(b1, av1, u.delta);
-    if (x.rr == u.ch && x.cc == u.cw0) {  // the updated coordinate itself keeps its value
-      const int kq = u.k0 / VE, ke = u.k0 % VE;
-      if (kq == 2 * x.q2) Vec<R>::set(b0, ke, Vec<R>::get(bold0, ke));
-      if (kq == 2 * x.q2 + 1) Vec<R>::set(b1, ke, Vec<R>::get(bold1, ke));
-    }
-  }
-  const long long e = ((long long)x.rr * I.W + x.cc) * I.KS + 2 * x.q2 * VE;
-  *reinterpret_cast<V *>(I.beta + e) = b0;
-  if (x.two) *reinterpret_cast<V *>(I.beta + e + VE) = b1;
-  R best = R(-1);
-  int bk = 0;
-  const int k0 = 2 * x.q2 * VE;
-  const V in0 = *reinterpret_cast<const V *>(P.sh_inv_n + k0);
-  const V in1 = x.two ? *reinterpret_cast<const V *>(P.sh_inv_n + k0 + VE) : Vec<R>::zero();
+  R best = R(0);
+  if (!__any(nz)) {
 #pragma unroll
-  for (int e2 = 0; e2 < 2 * VE; ++e2) {
-    const int k = k0 + e2;
-    const R bv = e2 < VE ? Vec<R>::get(b0, e2) : Vec<R>::get(b1, e2 - VE);
-    const R zv = e2 < VE ? Vec<R>::get(x.z0, e2) : Vec<R>::get(x.z1, e2 - VE);
-    const R zn = st_target(bv, I.lambda, e2 < VE ? Vec<R>::get(in0, e2) : Vec<R>::get(in1, e2 - VE), I.positive);
-    const R sc = k < I.K ? move_score(zv, zn, I.tol, I.certify) : R(-1);
-    if (sc > best) {
-      best = sc;
-      bk = k;
-    }
+    for (int i = 0; i < NG; ++i)
+#pragma unroll
+      for (int e = 0; e < VE; ++e) best = fmax(best, fabs(shrink(b[i][e], nlam, lam) * inv[i][e]));
+    return best;
   }
-  P.sh_ps[it] = best;
-  P.sh_pk[it] = (uint16_t)bk;
+#pragma unroll
+  for (int i = 0; i < NG; ++i)
+#pragma unroll
+    for (int e = 0; e < VE; ++e) {
+      const R zv = z[i][e];
+      const R zn = shrink(b[i][e], nlam, lam) * inv[i][e];
+      const R dz = fabs(zn - zv);
+      // a move that changes the support or the sign scores at least tolc
+      const R floor = zv != R(0) ? tolc : R(0);
+      best = fmax(best, with_sign(zn, zv) > R(0) ? dz : fmax(dz, floor));
+    }
+  return best;
 }
 
-template <class R, int NT>
-__device__ __forceinline__ void patch_union(const Inst<R> &I, const PatchCtx<R, NT> &P, const UCand<R> *uc, int nc,
-                                            int R1, int R2, int C1, int C2) {
-  constexpr int LBUF = PatchBuf<R>::N;
+template <class R>
+__device__ __forceinline__ void put_score(const PatchCtx<R> &P, GPtr<R> at, int lt, R v) {
+  if (P.ls) P.ls[lt] = v;
+  score_st((R *)at, v);
+}
+
+// One lane's part of a position: up to NG groups of beta, of the first
+// covering update's DtD row and, where the position holds non-zeros, of z.
+template <class R, int NG> struct PStage {
+  typename NVec<R>::T b[NG], a[NG], z[NG];
+  unsigned m;  // updates covering the position
+  bool nz;
+};
+
+// Applies updates to the rows [R1, R2) x columns [C1, C2) of this team's
+// region: beta -= delta * DtD row (eq. beta_update; the updated coordinate of
+// an update keeps its value), and the position's cached best score.  With
+// MULTI false every position is covered by the one update uc[0].  With MULTI
+// the updates covering a position are those of both its row's and its
+// column's mask, summed in increasing worker order as applying them one after
+// another would; positions none covers are left untouched.  Every thread of
+// the workgroup takes part, as number vt.
+//
+// An item of eight atoms costs about as many issue cycles as its memory round
+// trip, so the work per item is kept short: the lanes of a position are
+// neighbours whose shares of a row are contiguous (coalesced reads), (row,
+// column) and every byte offset step by constants (no division), the inverse
+// norms stay in registers, only the best score is formed (the atom of a
+// candidate is found when it is selected), and it is combined between the
+// lanes of a position by DPP.  The next item's reads are issued before the
+// current one is used.
+template <class R, int NT, int NG, bool MULTI>
+__device__ __forceinline__ void patch_lanes(const PatchCtx<R> &P, const UCand<R> *uc, int vt, int R1, int R2, int C1,
+                                            int C2) {
+  typedef typename NVec<R>::T V;
+  constexpr int VE = Vec<R>::N;
+  const int sh = P.sh, LP = 1 << sh, j = vt & (LP - 1), pstep = NT >> sh;
+  const int ncol = C2 - C1, npos = (R2 - R1) * ncol;
+  const unsigned KSB = (unsigned)P.KS * sizeof(R);
+  int p = vt >> sh;
+  if (p >= npos) return;
+  int row = div_small(p, ncol), col = p - row * ncol;
+  const int drow = div_small(pstep, ncol), dcol = pstep - drow * ncol;
+  // offsets of the position from (R1, C1): in positions, in the bitmask, in bytes of beta and of A
+  unsigned oe = (unsigned)row * P.W + col;
+  int lt = (R1 - P.a1 + row) * P.ext2 + (C1 - P.a2) + col;
+  unsigned ob = oe * KSB + 16u * j;
+  unsigned oa = ((unsigned)row * P.U2 + col) * KSB + 16u * j;
+  const unsigned doe = (unsigned)drow * P.W + dcol, woe = (unsigned)(P.W - ncol);
+  const unsigned dob = doe * KSB, wob = woe * KSB;
+  const unsigned doa = ((unsigned)drow * P.U2 + dcol) * KSB, woa = (unsigned)(P.U2 - ncol) * KSB;
+  const int dlt = drow * P.ext2 + dcol, wlt = P.ext2 - ncol;
+  const long long pos0 = (long long)R1 * P.W + C1;
+  const GPtr<char> bb = (GPtr<char>)(P.beta + pos0 * P.KS);
+  const GPtr<const char> zb = (GPtr<const char>)(P.z + pos0 * P.KS);
+  const int ar0 = (R1 * P.U2 + C1) * P.KS;  // element of A at (R1, C1) relative to an update's aoff
+  const GPtr<const char> ab = (GPtr<const char>)(P.A + (MULTI ? 0 : uc[0].aoff + ar0));
+  const bool vl = j + (NG - 1) * LP < P.G;  // the lane's last group exists
+  const R d0 = uc[0].delta;
+  // FP64 items and those of three groups hold too many registers to have two
+  // in flight: there an item is loaded when it is used.  So it is for the
+  // large patches of a single update, which are bound by the traffic past the
+  // L2 (4096^2 RGB image: 69.5 ms of rounds, 72.8 ms with the next item ahead).
+  constexpr bool kAhead = sizeof(R) == 4 && NG <= 2 && MULTI;
+  V inv[NG];
+  auto norms = [&]() {
+#pragma unroll
+    for (int i = 0; i < NG; ++i)
+      inv[i] = i < NG - 1 || vl ? *reinterpret_cast<const V *>(P.inv_n + (j + i * LP) * VE) : V(R(0));
+  };
+  if (kAhead) norms();
+  // single update: its own position in the patch
+  const int ps = MULTI ? -1
+                       : (uc[0].ch >= R1 && uc[0].ch < R2 && uc[0].cw0 >= C1 && uc[0].cw0 < C2
+                              ? (uc[0].ch - R1) * ncol + uc[0].cw0 - C1
+                              : -1);
+  auto load = [&](PStage<R, NG> &x, int rw, int cl, unsigned xb, unsigned xa, int xl) {
+    unsigned ua = xa;
+    x.m = 1u;
+    if (MULTI) {
+      x.m = P.rowm[rw] & P.colm[cl];
+      if (!x.m) return;
+      ua += (unsigned)(uc[__ffs(x.m) - 1].aoff + ar0) * (unsigned)sizeof(R);
+    }
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+      const bool on = i < NG - 1 || vl;
+      x.b[i] = on ? *(GPtr<const V>)(bb + xb + 16u * (i * LP)) : V(R(0));
+      x.a[i] = on ? *(GPtr<const V>)(ab + ua + 16u * (i * LP)) : V(R(0));
+    }
+    x.nz = P.nzb ? (P.nzb[xl >> 5] >> (xl & 31)) & 1u : true;
+    if (__any(x.nz)) {  // z is used only where a lane of the wave has non-zeros
+#pragma unroll
+      for (int i = 0; i < NG; ++i)
+        x.z[i] = x.nz && (i < NG - 1 || vl) ? *(GPtr<const V>)(zb + xb + 16u * (i * LP)) : V(R(0));
+    }
+  };
+  auto hold = [&](V *a, int k0) {  // the updated coordinate keeps its beta: no contribution there
+    const int kq = k0 / VE, ke = k0 - kq * VE;
+#pragma unroll
+    for (int i = 0; i < NG; ++i)
+#pragma unroll
+      for (int e = 0; e < VE; ++e) a[i][e] = kq == j + i * LP && e == ke ? R(0) : a[i][e];
+  };
+  const GPtr<R> sb = P.score + pos0;
+  // One item, loaded in x (or loaded here); the next one's loads go to y.
+  auto step = [&](PStage<R, NG> &x, PStage<R, NG> &y) {
+    if (!kAhead) load(x, row, col, ob, oa, lt);
+    const int pn = p + pstep;
+    int coln = col + dcol, rown = row + drow, ltn = lt + dlt;
+    unsigned oen = oe + doe, oan = oa + doa, obn = ob + dob;
+    if (coln >= ncol) {
+      coln -= ncol;
+      ++rown;
+      oen += woe;
+      obn += wob;
+      oan += woa;
+      ltn += wlt;
+    }
+    y.m = 0u;
+    if (kAhead && pn < npos) load(y, rown, coln, obn, oan, ltn);
+    if (x.m) {
+      V *const b = x.b;
+      if (!MULTI) {
+        if (p == ps) hold(x.a, uc[0].k0);
+#pragma unroll
+        for (int i = 0; i < NG; ++i)
+#pragma unroll
+          for (int e = 0; e < VE; ++e) b[i][e] = fma_neg(b[i][e], x.a[i][e], d0);
+      } else {
+        unsigned m = x.m;
+        for (;;) {
+          const UCand<R> &u = uc[__ffs(m) - 1];
+          m &= m - 1;
+          if (R1 + row == u.ch && C1 + col == u.cw0) hold(x.a, u.k0);
+          const R d = u.delta;
+#pragma unroll
+          for (int i = 0; i < NG; ++i)
+#pragma unroll
+            for (int e = 0; e < VE; ++e) b[i][e] = fma_neg(b[i][e], x.a[i][e], d);
+          if (!m) break;
+          const unsigned ua = oa + (unsigned)(uc[__ffs(m) - 1].aoff + ar0) * (unsigned)sizeof(R);
+#pragma unroll
+          for (int i = 0; i < NG; ++i)
+            x.a[i] = i < NG - 1 || vl ? *(GPtr<const V>)(ab + ua + 16u * (i * LP)) : V(R(0));
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NG; ++i)
+        if (i < NG - 1 || vl) *(GPtr<V>)(bb + ob + 16u * (i * LP)) = b[i];
+      if (!kAhead) norms();
+      const R best = lanes_max(lane_best<R, NG>(b, x.z, inv, x.nz, P.nlam, P.lam, P.tolc), sh);
+      if (j == 0) put_score(P, sb + oe, lt, best);
+    }
+    p = pn;
+    row = rown;
+    col = coln;
+    lt = ltn;
+    oe = oen;
+    ob = obn;
+    oa = oan;
+  };
+  PStage<R, NG> x, y;
+  if (kAhead) load(x, row, col, ob, oa, lt);
+  for (;;) {
+    step(x, y);
+    if (p >= npos) break;
+    if constexpr (kAhead) {
+      step(y, x);
+      if (p >= npos) break;
+    }
+  }
+}
+
+// patch_lanes for positions of more atom groups than a wave's lanes hold at
+// three each: the lanes of a wave loop over a position's groups.
+template <class R, int NT, bool MULTI>
+__device__ __forceinline__ void patch_wide(const PatchCtx<R> &P, const UCand<R> *uc, int vt, int R1, int R2, int C1,
+                                           int C2) {
+  typedef typename NVec<R>::T V;
+  constexpr int VE = Vec<R>::N;
+  const int lane = threadIdx.x & 63, ncol = C2 - C1, npos = (R2 - R1) * ncol;
+  for (int p = vt >> 6; p < npos; p += NT / 64) {
+    const int row = p / ncol, h = R1 + row, w = C1 + p - row * ncol;
+    const unsigned m0 = MULTI ? P.rowm[row] & P.colm[w - C1] : 1u;
+    if (!m0) continue;
+    const long long pos = (long long)h * P.W + w;
+    R best = R(0);
+    for (int q = lane; q < P.G; q += 64) {
+      const long long e = pos * P.KS + q * VE;
+      V b = *(GPtr<const V>)(P.beta + e);
+      const V z = *(GPtr<const V>)(P.z + e), inv = *reinterpret_cast<const V *>(P.inv_n + q * VE);
+      for (unsigned m = m0; m; m &= m - 1) {
+        const UCand<R> &u = uc[__ffs(m) - 1];
+        const V a = *(GPtr<const V>)(P.A + (u.aoff + (h * P.U2 + w) * P.KS + q * VE));
+        const V old = b;
+#pragma unroll
+        for (int i = 0; i < VE; ++i) {
+          b[i] = fma_neg(b[i], a[i], u.delta);
+          if (h == u.ch && w == u.cw0 && u.k0 == q * VE + i) b[i] = old[i];
+        }
+      }
+      *(GPtr<V>)(P.beta + e) = b;
+      best = fmax(best, lane_best<R, 1>(&b, &z, &inv, true, P.nlam, P.lam, P.tolc));
+    }
+    best = lanes_max(best, 6);
+    if (lane == 0) put_score(P, P.score + pos, (h - P.a1) * P.ext2 + w - P.a2, best);
+  }
+}
+
+template <class R, int NT, int NG, bool MULTI>
+__device__ __forceinline__ void patch_rect(const PatchCtx<R> &P, const UCand<R> *uc, int vt, int R1, int R2, int C1,
+                                           int C2) {
+  if constexpr (NG == 0) {
+    patch_wide<R, NT, MULTI>(P, uc, vt, R1, R2, C1, C2);
+  } else {
+    // bands of rows whose byte offsets stay below 2^31 (one band unless rows are huge)
+    const long long pitch = (long long)max(P.W, P.U2) * P.KS * (long long)sizeof(R);
+    const int rows = (int)max(1ll, min(1ll << 20, ((1ll << 31) - 1) / pitch - 1));
+    for (int r = R1; r < R2; r += rows) patch_lanes<R, NT, NG, MULTI>(P, uc, vt, r, min(r + rows, R2), C1, C2);
+  }
+}
+
+// Every update of `uc` in one pass over the bounding box of their patches, in
+// blocks whose row and column masks fit the LDS tables.
+template <class R, int NT, int NG>
+__device__ __forceinline__ void patch_union(const PatchCtx<R> &P, const UCand<R> *uc, int nc, int R1, int R2, int C1,
+                                            int C2) {
   const int tid = threadIdx.x;
-  const int W = I.W, G2 = (P.G + 1) / 2;
-  const int rowstride = I.U2 * I.KS;
-  const int ncol = C2 - C1;
-  const int cw = min(min(ncol, LBUF / G2), kMaskCols);
-  const int rc = max(1, min(kMaskRows, LBUF / (cw * G2)));
+  const long long pitch = (long long)max(P.W, P.U2) * P.KS * (long long)sizeof(R);
+  const int rc = (int)max(1ll, min((long long)kMaskRows, ((1ll << 31) - 1) / pitch - 1));
   for (int rr0 = R1; rr0 < R2; rr0 += rc) {
-    const int rr1 = min(rr0 + rc, R2);
-    for (int cc0 = C1; cc0 < C2; cc0 += cw) {
-      const int ccw = min(cw, C2 - cc0);
-      const int nrow = rr1 - rr0, npos = nrow * ccw;
-      for (int j = tid; j < nrow + ccw; j += NT) {
+    const int rr1 = min(rr0 + rc, R2), nrow = rr1 - rr0;
+    for (int cc0 = C1; cc0 < C2; cc0 += kMaskCols) {
+      const int cc1 = min(cc0 + kMaskCols, C2);
+      if (rr0 != R1 || cc0 != C1) __syncthreads();
+      for (int j = tid; j < nrow + cc1 - cc0; j += NT) {
         unsigned mk = 0;
         if (j < nrow) {
           for (int c = 0; c < nc; ++c)
@@ -508,647 +649,961 @@ __device__ __forceinline__ void patch_union(const Inst<R> &I, const PatchCtx<R, 
         }
       }
       __syncthreads();
-      const int ng = ccw * G2, nit = npos * G2;
-      const unsigned mng = rcp_of(ng), mg = rcp_of(G2), rcw = rcp_of(ccw);
-#pragma unroll 1
-      for (int it = tid; it < nit; it += NT) {
-        PItem<R> x;
-        pitem_load<R, NT>(I, P, uc, it, nit, rr0, cc0, ng, G2, mng, mg, rowstride, x);
-        if (!x.m) P.sh_ps[it] = R(-2);  // no update covers this position: its cache stays
-        pitem_apply<R, NT>(I, P, uc, it, rowstride, x);
-      }
-      __syncthreads();
-      for (int t = tid; t < npos; t += NT) {
-        const R *pp = P.sh_ps + t * G2;
-        if (pp[0] == R(-2)) continue;
-        const int tr = div_rcp(t, ccw, rcw);
-        const int pos = (rr0 + tr) * W + cc0 + (t - tr * ccw);
-        const uint16_t *pk = P.sh_pk + t * G2;
-        R best = pp[0];
-        int bk = pk[0];
-        for (int g = 1; g < G2; ++g)
-          if (pp[g] > best) {
-            best = pp[g];
-            bk = pk[g];
-          }
-        score_st(I.score + pos, best);
-        reinterpret_cast<uint16_t *>(I.meta + pos)[0] = (uint16_t)bk;  // the atom half of meta
-      }
-      __syncthreads();
+      patch_rect<R, NT, NG, true>(P, uc, tid, rr0, rr1, cc0, cc1);
     }
   }
 }
 
-// One workgroup is one worker of Alg. 3 (DiCoDiLe-Z).  Worker w of an instance
-// owns S_w, a block of a W1 x W2 balanced split of the valid domain, cut into
-// Mw balanced sub-domains of about tile1 x tile2 positions that it visits
-// cyclically.
+// Sets or clears a position's bit (other workers of the team may change
+// other bits of the word).
+__device__ __forceinline__ void nzb_put(uint32_t *nzb, int t, bool on) {
+  if (!nzb) return;
+  if (on)
+    atomicOr(&nzb[t >> 5], 1u << (t & 31));
+  else
+    atomicAnd(&nzb[t >> 5], ~(1u << (t & 31)));
+}
+
+// The instance read through the constant address space (scalar loads), from a
+// pointer the compiler cannot see through: what a phase derives from it is
+// loaded and derived again in each phase of each round.  Without this the
+// compiler keeps every loop-invariant of every phase in registers and spills
+// those the patch loop needs.
+template <class R> using CInst = const __attribute__((address_space(4))) Inst<R>;
+template <class R> __device__ __forceinline__ CInst<R> *fresh(CInst<R> *p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Largest value over a wave; smallest int over a wave: rows of 16 lanes by
+// DPP, the four rows by lane reads.
+template <class R> __device__ __forceinline__ R read_lane(R v, int l);
+template <> __device__ __forceinline__ float read_lane<float>(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+template <> __device__ __forceinline__ double read_lane<double>(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+template <int CTRL> __device__ __forceinline__ int dpp_mov_i(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+}
+// Largest score of a wave.  Scores are not negative but for the marker -1, so
+// FP32 ones order like their bits.
+__device__ __forceinline__ float wave_max(float f) {
+  int v = __float_as_int(f);
+  v = max(v, dpp_mov_i<0xB1>(v));
+  v = max(v, dpp_mov_i<0x4E>(v));
+  v = max(v, dpp_mov_i<0x141>(v));
+  v = max(v, dpp_mov_i<0x140>(v));
+  return __int_as_float(max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+                            max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48))));
+}
+__device__ __forceinline__ double wave_max(double v) {
+  v = lanes_max(v, 4);
+  return fmax(fmax(read_lane<double>(v, 0), read_lane<double>(v, 16)),
+              fmax(read_lane<double>(v, 32), read_lane<double>(v, 48)));
+}
+__device__ __forceinline__ int wave_min(int v) {
+  v = min(v, dpp_mov_i<0xB1>(v));
+  v = min(v, dpp_mov_i<0x4E>(v));
+  v = min(v, dpp_mov_i<0x141>(v));
+  v = min(v, dpp_mov_i<0x140>(v));
+  return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+             min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+// Largest (score, lowest position) over a wave, in every lane.  Called by
+// whole waves.
+template <class R> __device__ __forceinline__ void wave_argmax(R &s, int &pos) {
+  const R m = wave_max(s);
+  pos = wave_min(s == m ? pos : 0x7fffffff);
+  s = m;
+}
+
+// The best move at position `pos` (the lowest atom among equal scores, as the
+// caches have it), found by one whole wave from beta and z: its atom, the
+// coordinate's value and its target.
+template <class R>
+__device__ __forceinline__ void best_move(CInst<R> *I, const R *inv_n, long long pos, int *k0, R *zc, R *zn) {
+  const int lane = threadIdx.x & 63, K = I->K;
+  const GPtr<const R> zp = as_global((const R *)I->z) + pos * I->KS, bp = as_global((const R *)I->beta) + pos * I->KS;
+  R bs = R(-1), bz = R(0), bt = R(0);
+  int bk = 0x7fffffff;
+  for (int k = lane; k < K; k += 64) {
+    const R zv = zp[k];
+    const R t = st_target((R)bp[k], (R)I->lambda, inv_n[k], I->positive);
+    const R sc = move_score(zv, t, (R)I->tol, I->certify);
+    if (sc > bs) {
+      bs = sc;
+      bk = k;
+      bz = zv;
+      bt = t;
+    }
+  }
+  R ms = bs;
+  int mk = bk;
+  wave_argmax(ms, mk);
+  *k0 = mk;
+  *zc = read_lane<R>(bz, mk & 63);
+  *zn = read_lane<R>(bt, mk & 63);
+}
+
+// One workgroup is a team: it runs a block of G1 x G2 neighbouring workers of
+// Alg. 3 (DiCoDiLe-Z).  Worker w of an instance owns S_w, a block of a W1 x W2
+// balanced split of the valid domain, cut into Mw balanced sub-domains of
+// about tile1 x tile2 positions that it visits cyclically.  The team owns the
+// region of its workers' blocks.
 //
-// Neighbours read the scores of S_w's border band (positions within L_i - 1
-// of a side shared with a neighbour) in their soft-lock tests.  A round runs:
-//   A  visit `inner` sub-domains (Alg. 1's local greedy choice).  Candidates
-//      whose patch stays clear of the band concern no other worker
-//      (eq. soft_lock only applies near the border): they are applied at once.
-//      The first band-reaching candidate is held; it is tested against the
-//      other workers' scores in V(w0) when V(w0) leaves S_w (eq. soft_lock,
-//      lower worker index wins a tie) and published, tagged with the round;
-//   B  every worker applies, to the part of beta, z and the cache it owns, the
-//      accepted published candidates of itself and of its grid neighbours
-//      whose neighbourhood meets S_w (eq. beta_update), in increasing worker
-//      order, then publishes progress r + 1.
-// Phase A of round r reads the band of S_w's neighbours, which only they
-// write, in their phase B: it starts once each neighbour's progress is >= r.
-// A neighbour starts its phase B of round r only after reading this worker's
-// round-r candidate, published after this worker's phase A reads.  Worker
-// sizes of at least L_i keep every interaction between grid neighbours.
+// A round runs:
+//   A  every worker visits `inner` sub-domains (Alg. 1's local greedy choice),
+//      a group of waves per worker.  With several visits, candidates whose
+//      patch stays clear of the border band (which other workers read) are
+//      applied at once and the first band-reaching one is held.  The held
+//      candidate is tested against the other workers' scores in V(w0) when
+//      V(w0) leaves S_w (eq. soft_lock, lower worker index wins a tie) and
+//      published, tagged with the round;
+//   B  the team applies, to the part of beta, z and the cache it owns, the
+//      accepted candidates of its workers and of the ring of workers around
+//      them whose neighbourhood meets its region (eq. beta_update), in
+//      increasing worker order, all its waves on each patch, then publishes
+//      progress r + 1.
+// Phase A of round r reads scores of the neighbouring teams' border bands,
+// which only they write, in their phase B: it does so once each neighbour's
+// progress is >= r.  A neighbour starts its phase B of round r only after
+// reading this team's round-r candidates, published after this team's phase A
+// reads.  Worker sizes of at least L_i keep every interaction between grid
+// neighbours.
+//
+// Why teams: the patches of a round fall unevenly on the workers, and a round
+// lasts as long as the slowest worker of a neighbourhood.  A worker per
+// workgroup left a quarter of a CU's waves on each patch while the CU's other
+// workers waited; a team of the CU's workers puts all of them on every patch,
+// and its workers read each other's scores and candidates without a wait
+// between workgroups.  The order of the updates at every position, and so
+// every result, is that of one worker per workgroup.
 //
 // Stopping: a worker is quiet once its last Mw visits found no move scoring
 // >= tol and no patch touched S_w since (random rule: once the scan at the
 // end of its last epoch found none and no patch touched S_w since).  When
 // every worker reports quiet at the end of the same round, every
 // coordinate's move is below tol and no further update can happen: all
-// workers exit.
+// teams exit.
 //
 // Under the random rule a candidate's score is that of its drawn coordinate,
 // at most the cached best of its position, so of two interacting candidates
 // the soft-lock test still rejects at least one: each sees the other's
 // position holding a score >= its own (ties go to the lower worker index).
-template <class R, int NT> struct RoundSmem {
-  static constexpr int LBUF = PatchBuf<R>::N;
-  R ps[LBUF];
-  uint16_t pk[LBUF];
-  uint32_t nzb[kNzWords];
-  uint32_t rowm[kMaskRows], colm[kMaskCols];
-  R inv_n[1024];
-  R rs[NT / 64];
-  int ri[NT / 64];
-  int exit_f, cok;
-  int wok[9];  // per-neighbour result of the progress wait
-  int ck0;       // the held candidate's atom, current value and target
-  R czc, czn;
-  uint32_t cmeta;  // ... and its position's meta word (LGCD rules)
-  UCand<R> ui;  // an interior candidate applied within phase A
-  int nbr[9];
-  UCand<R> uc[9];
-  int nuc, ub[4];  // updates touching S_w and the bounding box of their patches
-  int ub_union;    // 1: apply them in one pass over the bounding box
+// What a team keeps of one of its workers between phases.
+struct TeamWorker {
+  int w, a1, b1, a2, b2;  // worker index and block
+  int nb1, nb2;           // sub-domains per axis: about extent / tile, balanced (sizes differ by <= 1)
+  int mcur, quiet;        // the next sub-domain; consecutive visits with no move >= tol and no patch of S_w
+  int s1, e1, s2, e2;     // rows [s1, e1) x columns [s2, e2) of the next sub-domain
+  long long cursor;       // visits so far
+  unsigned upd, cand, lock, visit;
+  unsigned long long chk, patch;
 };
 
-// Runs worker w of instance I until its instance converges or stops.  Every
-// thread of the workgroup calls it.
-template <class R, int NT>
-__device__ void run_worker(const Inst<R> &I, const int w, const long long timeout_ticks, RoundSmem<R, NT> &sm) {
-  constexpr int VE = Vec<R>::N;
-  R *const sh_inv_n = sm.inv_n;
-  R *const sh_rs = sm.rs;
-  int *const sh_ri = sm.ri;
-  int &sh_exit = sm.exit_f;
-  int &sh_cok = sm.cok;
-  int *const sh_nbr = sm.nbr;
-  const int tid = threadIdx.x;
-  const int nW = I.W1 * I.W2;
-  const int wi = w / I.W2, wj = w - wi * I.W2;
-  const int K = I.K, H = I.H, W = I.W;
-  const int a1 = part_start(wi, H, I.W1), b1 = part_start(wi + 1, H, I.W1);
-  const int a2 = part_start(wj, W, I.W2), b2 = part_start(wj + 1, W, I.W2);
-  // sub-domains: about extent / tile per axis, balanced (sizes differ by <= 1)
-  const int ext1 = b1 - a1, ext2 = b2 - a2;
-  const int nb1 = max(1, (ext1 + I.tile1 / 2) / I.tile1), nb2 = max(1, (ext2 + I.tile2 / 2) / I.tile2);
-  const int Mw = nb1 * nb2;
-  // random rule: one drawn coordinate per round; a scan of S_w every npw
-  // draws (an epoch) decides whether the worker is quiet
-  const bool rnd = I.strategy == 3;
-  const int npw = ext1 * ext2;
-  const int inner = rnd ? 1 : (I.inner > 0 ? min(I.inner, Mw) : 1);
-  const int qthr = rnd ? 1 : Mw;  // quiet count of a worker with no pending move
-  // candidates at w0 in [in_lo, in_hi[ patch nothing of the band neighbours read
-  const int in_lo1 = wi > 0 ? a1 + 2 * (I.L1 - 1) : a1, in_hi1 = wi < I.W1 - 1 ? b1 - 2 * (I.L1 - 1) : b1;
-  const int in_lo2 = wj > 0 ? a2 + 2 * (I.L2 - 1) : a2, in_hi2 = wj < I.W2 - 1 ? b2 - 2 * (I.L2 - 1) : b2;
+template <class R, int NT> struct TeamSmem {
+  // positions of a region whose scores are also kept in LDS
+  static constexpr int kScores = (NT == 1024 ? 65536 : 16384) / (int)sizeof(R);
+  R score[kScores];
+  R inv_n[1024];
+  uint32_t nzb[kNzWords];
+  uint32_t rowm[kMaskRows], colm[kMaskCols];
+  UCand<R> uc[kUpdMax];
+  UCand<R> ui[kTeamMax];  // interior candidates applied within phase A
+  TeamWorker wk[kTeamMax];
+  R ps[NT / 64];          // per-wave partial selections
+  int pp[NT / 64];
+  R cs[kTeamMax];         // candidates under test: score, position, soft-lock outcome
+  int cp[kTeamMax], clk[kTeamMax];
+  int done[kTeamMax];     // 1: the worker is quiet
+  int ion[kTeamMax];      // interior candidate of the current visit
+  int A1, B1, A2, B2;     // the region
+  int nbt[9];             // the neighbouring teams (-1: none, or this one)
+  int ncn, cnw[kUpdMax], cnt[kUpdMax];  // the workers whose updates can touch the region, in order; their teams
+  int nuc, ub[4], ub_union;
+  unsigned long long patched;  // positions of beta patched in phase B
+  int bad, exit_f;
+  unsigned long long tk[4], mark;  // phase times: wait, select, collect, apply
+};
 
-  PatchCtx<R, NT> P;
-  P.sh_ps = sm.ps;
-  P.sh_pk = sm.pk;
-  P.sh_inv_n = sh_inv_n;
+// Bounds of a worker's next sub-domain (its divisions are kept off the path
+// between a round's end and the next selection).
+__device__ __forceinline__ void next_visit(TeamWorker &k) {
+  const int bi = k.mcur / k.nb2, bj = k.mcur - bi * k.nb2, e1w = k.b1 - k.a1, e2w = k.b2 - k.a2;
+  k.s1 = k.a1 + part_start_fast(bi, e1w, k.nb1);
+  k.e1 = k.a1 + part_start_fast(bi + 1, e1w, k.nb1);
+  k.s2 = k.a2 + part_start_fast(bj, e2w, k.nb2);
+  k.e2 = k.a2 + part_start_fast(bj + 1, e2w, k.nb2);
+}
+
+// Adds the time since the last mark to one phase's, by one thread: one round
+// in kTimed is timed (reading the clock takes a good part of a short phase).
+constexpr int kTimed = 16;
+template <class R, int NT> __device__ __forceinline__ void team_mark(TeamSmem<R, NT> &sm, int r, int phase) {
+  if (r & (kTimed - 1)) return;
+  const unsigned long long t = __builtin_amdgcn_s_memrealtime();
+  if (phase >= 0) sm.tk[phase] += t - sm.mark;
+  sm.mark = t;
+}
+
+// The soft-lock test of a candidate of score `bs` at (ch, cw) of the worker
+// [a1, b1) x [a2, b2): whether a position of V(w0) outside its block holds a
+// larger score, or an equal one owned by a lower worker (eq. soft_lock), over
+// the positions of the waves gw, gw + nw, ... of V(w0).  Scores of the team's
+// own region come from LDS where it keeps them.  Whole waves call it.
+template <class R, int NT>
+__device__ __forceinline__ bool soft_test(CInst<R> *I, const TeamSmem<R, NT> &sm, bool ls, int w, int a1, int b1,
+                                          int a2, int b2, R bs, int ch, int cw, int gw, int nw) {
+  const int H = I->H, W = I->W, lane = threadIdx.x & 63;
+  const int A1 = uni(sm.A1), B1 = uni(sm.B1), A2 = uni(sm.A2), B2 = uni(sm.B2);
+  const int v1 = max(ch - I->L1 + 1, 0), u1 = min(ch + I->L1, H);
+  const int v2 = max(cw - I->L2 + 1, 0), u2 = min(cw + I->L2, W);
+  const int vw = u2 - v2, nv = (u1 - v1) * vw, gs = 64 * nw;
+  R *const sg = I->score;
+  constexpr int U = 8;  // positions per pass, their loads in flight together
+  const int dh = div_small(gs, vw), dw = gs - dh * vw;
+  int th = v1 + div_small(gw * 64 + lane, vw), tw = v2 + gw * 64 + lane - (th - v1) * vw;
+  for (int t = gw * 64; t < nv; t += U * gs) {
+    R sc[U];
+    const int th0 = th, tw0 = tw;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      sc[u] = R(-1);
+      if (t + u * gs < nv) {  // the same for the whole wave
+        const bool mine = th >= a1 && th < b1 && tw >= a2 && tw < b2;
+        if (t + u * gs + lane < nv && !mine) {
+          if (ls && th >= A1 && th < B1 && tw >= A2 && tw < B2)
+            sc[u] = sm.score[(th - A1) * (B2 - A2) + tw - A2];
+          else
+            sc[u] = score_ld(sg + (long long)th * W + tw);
+        }
+        tw += dw;
+        th += dh;
+        if (tw >= u2) {
+          tw -= vw;
+          ++th;
+        }
+      }
+    }
+    R mx = sc[0];
+#pragma unroll
+    for (int u = 1; u < U; ++u) mx = sc[u] > mx ? sc[u] : mx;
+    if (__any(mx > bs)) return true;
+    if (__any(mx == bs)) {  // ties: the owners decide
+      th = th0;
+      tw = tw0;
+      bool lk = false;
+#pragma unroll 1
+      for (int u = 0; u < U; ++u) {
+        R sv = sc[0];
+#pragma unroll
+        for (int v = 1; v < U; ++v) sv = u == v ? sc[v] : sv;
+        if (sv == bs && part_owner(th, H, I->W1) * I->W2 + part_owner(tw, W, I->W2) < w) lk = true;
+        tw += dw;
+        th += dh;
+        if (tw >= u2) {
+          tw -= vw;
+          ++th;
+        }
+      }
+      if (__any(lk)) return true;
+    }
+  }
+  return false;
+}
+
+// The candidate a worker's lead wave holds.
+template <class R> struct Held {
+  bool has = false;
+  R bs = R(-1), zc = R(0), zn = R(0);
+  int bp = 0, k0 = 0;
+};
+
+// One visit's selection: the best score of worker q's next sub-domain, over the
+// positions of the group's wave `gw` of `wpl` (Alg. 1's local greedy choice).
+template <class R, int NT>
+__device__ __forceinline__ void scan_visit(CInst<R> *I, const TeamSmem<R, NT> &sm, bool ls, int q, int gw, int wpl,
+                                           R &vs, int &vp) {
+  const TeamWorker &k = sm.wk[q];
+  const int W = I->W, A1 = uni(sm.A1), A2 = uni(sm.A2), ext2 = uni(sm.B2) - A2;
+  const int s1 = uni(k.s1), e1 = uni(k.e1), s2 = uni(k.s2), e2 = uni(k.e2);
+  const int bw = e2 - s2, np = (e1 - s1) * bw, gs = 64 * wpl;
+  const GPtr<const R> sg = as_global((const R *)I->score);
+  // eight positions per pass with their loads in flight together; the (row,
+  // column) of position t steps by the group's lanes each time
+  constexpr int U = 8;
+  const int lane = threadIdx.x & 63;
+  const int dh = div_small(gs, bw), dw = gs - dh * bw;
+  int th = div_small(gw * 64 + lane, bw), tw = gw * 64 + lane - th * bw;
+  for (int t = gw * 64; t < np; t += U * gs) {
+    R sc[U];
+    int ps[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      sc[u] = R(-1);
+      if (t + u * gs < np) {  // the same for the whole wave
+        ps[u] = (s1 + th) * W + s2 + tw;
+        if (t + u * gs + lane < np) sc[u] = ls ? sm.score[(s1 - A1 + th) * ext2 + s2 - A2 + tw] : sg[ps[u]];
+        tw += dw;
+        th += dh;
+        if (tw >= bw) {
+          tw -= bw;
+          ++th;
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (t + u * gs < np && sc[u] > vs) {  // a lane's positions ascend: the first of equal scores stays
+        vs = sc[u];
+        vp = ps[u];
+      }
+  }
+  wave_argmax(vs, vp);
+}
+
+// z and the non-zero count of a coordinate that moves, and the divergence guard.
+template <class R, int NT>
+__device__ __forceinline__ void move_z(CInst<R> *I, TeamSmem<R, NT> &sm, bool nzb, int pos, int h, int w, int k0,
+                                       R zc, R zn) {
+  as_global(I->z)[(long long)pos * I->KS + k0] = zn;
+  const GPtr<uint32_t> mg = as_global(I->meta) + pos;
+  const int nzc = meta_nzc(*mg) + (zn != R(0)) - (zc != R(0));
+  *mg = meta_pack(nzc);
+  if (nzb) nzb_put(sm.nzb, (h - sm.A1) * (sm.B2 - sm.A2) + (w - sm.A2), nzc != 0);
+  const R guard = I->div_guard;
+  if (guard > R(0) && (zn > guard || -zn > guard)) {
+    st_shared_i32(&I->ctl->stop, 1);
+    atomicCAS(&I->ctl->status, 0, 2);
+  }
+}
+
+// A further visit of a round with several (`inner` > 1): interior candidates are
+// handed to the whole team, the first band-reaching one is held.
+template <class R, int NT>
+__device__ __forceinline__ void visit_multi(CInst<R> *I, TeamSmem<R, NT> &sm, bool nzb, int q, R vs, int vp,
+                                            Held<R> &c, long long visit, long long &restart) {
+  TeamWorker &k = sm.wk[q];
+  const int L1 = I->L1, L2 = I->L2, W = I->W;
+  const int a1 = uni(k.a1), b1 = uni(k.b1), a2 = uni(k.a2), b2 = uni(k.b2);
+  const int wi = uni(k.w) / I->W2, wj = uni(k.w) - wi * I->W2;
+  const int h0 = vp / W, w0 = vp - h0 * W;
+  // candidates in [in_lo, in_hi[ patch nothing of the band neighbours read
+  const int in_lo1 = wi > 0 ? a1 + 2 * (L1 - 1) : a1, in_hi1 = wi < I->W1 - 1 ? b1 - 2 * (L1 - 1) : b1;
+  const int in_lo2 = wj > 0 ? a2 + 2 * (L2 - 1) : a2, in_hi2 = wj < I->W2 - 1 ? b2 - 2 * (L2 - 1) : b2;
+  if (!(h0 >= in_lo1 && h0 < in_hi1 && w0 >= in_lo2 && w0 < in_hi2)) {
+    if (!c.has) {
+      c.has = true;
+      c.bs = vs;
+      c.bp = vp;
+    } else if (restart < 0) {
+      restart = visit;  // a second band-reaching candidate waits for the next round
+    }
+    return;
+  }
+  if (c.has && abs(h0 - c.bp / W) < L1 && abs(w0 - c.bp % W) < L2) {  // would interact with the held one
+    if (restart < 0) restart = visit;
+    return;
+  }
+  int k0 = 0;
+  R zc = R(0), zn = R(0);
+  best_move<R>(I, sm.inv_n, vp, &k0, &zc, &zn);
+  if ((threadIdx.x & 63) == 0) {
+    move_z<R, NT>(I, sm, nzb, vp, h0, w0, k0, zc, zn);
+    UCand<R> &u = sm.ui[q];
+    u.k0 = k0;
+    u.ch = h0;
+    u.cw0 = w0;
+    u.r1 = max(h0 - L1 + 1, a1);
+    u.r2 = min(h0 + L1, b1);
+    u.c1 = max(w0 - L2 + 1, a2);
+    u.c2 = min(w0 + L2, b2);
+    u.aoff = ((k0 * I->U1 - h0 + L1 - 1) * I->U2 - w0 + L2 - 1) * I->KS;
+    u.delta = zn - zc;
+    k.patch += (unsigned long long)(u.r2 - u.r1) * (u.c2 - u.c1);
+    k.upd += 1;
+    sm.ion[q] = 1;
+  }
+}
+
+// Collects this round's candidates of the workers whose updates can touch the
+// region (the team's own and the ring around it), clipped to the region, in
+// increasing worker order: the work list of phase B.  Run by one wave.
+template <class R, int NT>
+__device__ __forceinline__ void collect(CInst<R> *I, TeamSmem<R, NT> &sm, int r, long long timeout_ticks) {
+  const int lane = threadIdx.x & 63;
+  const int W = I->W, L1 = I->L1, L2 = I->L2;
+  const int A1 = uni(sm.A1), B1 = uni(sm.B1), A2 = uni(sm.A2), B2 = uni(sm.B2);
+  bool uval = false;
+  int uk0 = 0, uch = 0, ucw = 0, ur1 = 0, ur2 = 0, uc1 = 0, uc2 = 0;
+  R udl = R(0);
+  if (lane < sm.ncn) {
+    const unsigned long long *const c = I->cand + (long long)kCandWords * sm.cnw[lane];
+    const int *const pr = I->prog + sm.cnt[lane];
+    unsigned long long t = 0, d1 = 0, d2 = 0;
+    const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+    const int rtag = r & ((1 << kRoundBits) - 1);
+    for (;;) {
+      // all words and the team's progress are read together, one round trip per poll
+      t = ld_shared_u64(c);
+      d1 = ld_shared_u64(c + 1);
+      d2 = sizeof(R) == 8 ? ld_shared_u64(c + 2) : d1;
+      const int pg = ld_shared_i32(pr);
+      if (tag_round(t) == rtag && (int)(d1 >> 32) == r && (int)(d2 >> 32) == r) break;
+      if (pg == 0x7fffffff) {
+        // the worker's team has left; it stored its last words before its
+        // progress word, so words of this round are seen by a reread
+        t = ld_shared_u64(c);
+        d1 = ld_shared_u64(c + 1);
+        d2 = sizeof(R) == 8 ? ld_shared_u64(c + 2) : d1;
+        if (tag_round(t) != rtag || (int)(d1 >> 32) != r || (int)(d2 >> 32) != r) t = cand_tag(r, 0, kNoPos);
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+      if ((long long)(__builtin_amdgcn_s_memrealtime() - t0) > timeout_ticks) {
+        sm.bad = 1;
+        t = cand_tag(r, 0, kNoPos);
+        break;
+      }
+    }
+    const unsigned cpos = tag_pos(t);
+    if (cpos != kNoPos) {
+      udl = bits_delta<R>(sizeof(R) == 8 ? (d1 & 0xffffffffull) | (d2 << 32) : d1);
+      uk0 = tag_k0(t);
+      uch = (int)(cpos / (unsigned)W);
+      ucw = (int)(cpos - (unsigned)uch * (unsigned)W);
+      ur1 = max(uch - L1 + 1, A1);
+      ur2 = min(uch + L1, B1);
+      uc1 = max(ucw - L2 + 1, A2);
+      uc2 = min(ucw + L2, B2);
+      uval = ur1 < ur2 && uc1 < uc2;
+    }
+  }
+  const unsigned long long bal = __ballot(uval);
+  const int nu = __popcll(bal);
+  if (uval) {
+    UCand<R> &u = sm.uc[__popcll(bal & ((1ull << lane) - 1ull))];
+    u.k0 = uk0;
+    u.ch = uch;
+    u.cw0 = ucw;
+    u.r1 = ur1;
+    u.r2 = ur2;
+    u.c1 = uc1;
+    u.c2 = uc2;
+    u.aoff = ((uk0 * I->U1 - uch + L1 - 1) * I->U2 - ucw + L2 - 1) * I->KS;
+    u.delta = udl;
+  }
+  __builtin_amdgcn_wave_barrier();
+  // bounding box and area of the patches, over the lanes (at most 32 workers)
+  int x1 = uval ? ur1 : B1, x2 = uval ? ur2 : A1, y1 = uval ? uc1 : B2, y2 = uval ? uc2 : A2;
+  unsigned pa = uval ? (unsigned)((ur2 - ur1) * (uc2 - uc1)) : 0u;
+#pragma unroll
+  for (int off = 16; off > 0; off >>= 1) {
+    x1 = min(x1, __shfl_xor(x1, off, 32));
+    x2 = max(x2, __shfl_xor(x2, off, 32));
+    y1 = min(y1, __shfl_xor(y1, off, 32));
+    y2 = max(y2, __shfl_xor(y2, off, 32));
+    pa += __shfl_xor(pa, off, 32);
+  }
+  // One pass over the bounding box pays for small patches, whose cost is
+  // mostly per-update latency (positions no update covers cost no loads).
+  // Large patches (over 1024 positions) are bandwidth-bound and go one by
+  // one.  (The pass addresses the apply table with 32-bit byte offsets.)
+  const bool un = nu > 1 && (long long)I->U1 * I->U2 <= 1024 &&
+                  (long long)I->K * I->U1 * I->U2 * I->KS * (long long)sizeof(R) < (1ll << 31);
+  if (lane < nu && !un) {
+    unsigned ov = 0;
+    const UCand<R> &u = sm.uc[lane];
+    for (int c = 0; c < lane; ++c) {
+      const UCand<R> &o = sm.uc[c];
+      if (o.r1 < u.r2 && u.r1 < o.r2 && o.c1 < u.c2 && u.c1 < o.c2) ov |= 1u << c;
+    }
+    sm.uc[lane].ov = ov;
+  }
+  if (lane == 0) {
+    sm.nuc = nu;
+    sm.ub[0] = x1;
+    sm.ub[1] = x2;
+    sm.ub[2] = y1;
+    sm.ub[3] = y2;
+    sm.patched += pa;
+    sm.ub_union = un;
+  }
+}
+
+// What the patch loops need, derived where they run.
+template <class R, int NT>
+__device__ __forceinline__ PatchCtx<R> patch_ctx(CInst<R> *I, TeamSmem<R, NT> &sm, bool ls, bool nzb) {
+  PatchCtx<R> P;
+  P.beta = as_global(I->beta);
+  P.z = as_global((const R *)I->z);
+  P.A = as_global(I->A);
+  P.score = as_global(I->score);
+  P.ls = ls ? sm.score : nullptr;
   P.rowm = sm.rowm;
   P.colm = sm.colm;
-  P.G = I.KS / VE;
-  P.a1 = a1;
-  P.a2 = a2;
-  P.ext2 = ext2;
-  P.nzb = npw <= 32 * kNzWords ? sm.nzb : nullptr;
-  if (P.nzb)
-    for (int wd = tid; wd < (npw + 31) / 32; wd += NT) {
-      uint32_t m = 0;
-      for (int b = 0; b < 32; ++b) {
-        const int t = wd * 32 + b;
-        if (t < npw && meta_nzc(I.meta[(a1 + t / ext2) * W + a2 + t % ext2])) m |= 1u << b;
-      }
-      sm.nzb[wd] = m;
-    }
+  P.inv_n = sm.inv_n;
+  P.nzb = nzb ? sm.nzb : nullptr;
+  P.lam = I->lambda;
+  P.nlam = I->positive ? -R(__builtin_inf()) : -I->lambda;
+  P.tolc = I->certify ? I->tol : R(0);
+  P.W = I->W;
+  P.U2 = I->U2;
+  P.KS = I->KS;
+  P.G = I->KS / Vec<R>::N;
+  P.sh = I->lane_sh;
+  P.a1 = uni(sm.A1);
+  P.a2 = uni(sm.A2);
+  P.ext2 = uni(sm.B2) - P.a2;
+  return P;
+}
 
-  __syncthreads();
-  for (int k = tid; k < I.KS; k += NT) sh_inv_n[k] = k < K ? I.inv_n[k] : R(0);
-  if (tid == 0) {
-    int nn = 0;
-    for (int di = -1; di <= 1; ++di)
-      for (int dj = -1; dj <= 1; ++dj) {
-        const int ni = wi + di, nj = wj + dj;
-        if (ni >= 0 && ni < I.W1 && nj >= 0 && nj < I.W2) sh_nbr[nn++] = ni * I.W2 + nj;
+// EXT: the random rule and several visits per round (kept out of the usual
+// kernel, whose rounds are paced by the instructions of one wave).
+template <class R, int NT, int NG, bool EXT>
+__device__ __forceinline__ void run_team(CInst<R> *const I0, const int team, const long long timeout_ticks,
+                                         TeamSmem<R, NT> &sm) {
+  constexpr int NW = NT / 64;
+  // the last wave collects the candidates and the one before keeps the
+  // stopping consensus: with few workers per team neither leads one, so both
+  // wait on memory beside the leads
+  constexpr int kCollect = NW - 1, kConsensus = NT - 128;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+  int gn, wpl = 1;
+  bool ls, nzb;
+  {
+    CInst<R> *const I = fresh<R>(I0);
+    const int H = I->H, W = I->W;
+    const int ti = team / I->TW2, tj = team - ti * I->TW2;
+    const int w1a = ti * I->G1, g1 = min(I->G1, I->W1 - w1a), w2a = tj * I->G2, g2 = min(I->G2, I->W2 - w2a);
+    const int A1 = part_start(w1a, H, I->W1), B1 = part_start(w1a + g1, H, I->W1);
+    const int A2 = part_start(w2a, W, I->W2), B2 = part_start(w2a + g2, W, I->W2), ext2 = B2 - A2;
+    const long long nreg = (long long)(B1 - A1) * ext2;
+    gn = g1 * g2;
+    ls = nreg <= TeamSmem<R, NT>::kScores;
+    nzb = nreg <= 32 * kNzWords;
+    // Each worker has a group of wpl waves, the first of which leads (selects,
+    // tests, publishes).  One wave reads up to 512 positions of a sub-domain or
+    // of a V(w0); larger ones get more waves while they last.
+    const long long tp = max((long long)min(I->tile1, H) * min(I->tile2, W), (long long)I->U1 * I->U2);
+    int gp = 1;
+    while (gp < gn) gp <<= 1;
+    while (wpl * 2 * gp <= NW && (long long)wpl * 512 < tp) wpl <<= 1;
+    if (tid < gn) {
+      TeamWorker &k = sm.wk[tid];
+      const int wi = w1a + tid / g2, wj = w2a + tid % g2;
+      k.w = wi * I->W2 + wj;
+      k.a1 = part_start(wi, H, I->W1);
+      k.b1 = part_start(wi + 1, H, I->W1);
+      k.a2 = part_start(wj, W, I->W2);
+      k.b2 = part_start(wj + 1, W, I->W2);
+      k.nb1 = max(1, (k.b1 - k.a1 + I->tile1 / 2) / I->tile1);
+      k.nb2 = max(1, (k.b2 - k.a2 + I->tile2 / 2) / I->tile2);
+      k.cursor = I->wstate ? I->wstate[2 * k.w] : 0;
+      k.quiet = I->wstate ? (int)I->wstate[2 * k.w + 1] : 0;
+      k.mcur = (int)(k.cursor % (k.nb1 * k.nb2));
+      k.upd = k.cand = k.lock = k.visit = 0;
+      k.chk = k.patch = 0;
+      next_visit(k);
+    }
+    const GPtr<uint32_t> mg = as_global(I->meta);
+    const GPtr<const R> sg = as_global((const R *)I->score);
+    if (nzb)
+      for (int wd = tid; wd < (int)(nreg + 31) / 32; wd += NT) {
+        uint32_t m = 0;
+        for (int b = 0; b < 32; ++b) {
+          const int t = wd * 32 + b;
+          if (t < nreg && meta_nzc(mg[(A1 + t / ext2) * W + A2 + t % ext2])) m |= 1u << b;
+        }
+        sm.nzb[wd] = m;
       }
-    for (int q = nn; q < 9; ++q) sh_nbr[q] = -1;
+    if (ls)
+      for (int t = tid; t < (int)nreg; t += NT) sm.score[t] = sg[(A1 + t / ext2) * W + A2 + t % ext2];
+    for (int k = tid; k < I->KS; k += NT) sm.inv_n[k] = k < I->K ? I->inv_n[k] : R(0);
+    if (tid == 0) {
+      sm.A1 = A1;
+      sm.B1 = B1;
+      sm.A2 = A2;
+      sm.B2 = B2;
+      sm.bad = 0;
+      sm.patched = 0;
+      sm.exit_f = ld_shared_i32(&I->ctl->converged) | ld_shared_i32(&I->ctl->stop);
+      for (int i = 0; i < 4; ++i) sm.tk[i] = 0;
+    }
+    if (tid < 9) {
+      const int ni = ti + tid / 3 - 1, nj = tj + tid % 3 - 1;
+      sm.nbt[tid] =
+          tid != 4 && ni >= 0 && ni < I->TW1 && nj >= 0 && nj < I->TW2 ? ni * I->TW2 + nj : -1;
+    }
+    const int c1a = max(w1a - 1, 0), c1b = min(w1a + I->G1 + 1, I->W1);
+    const int c2a = max(w2a - 1, 0), c2b = min(w2a + I->G2 + 1, I->W2), cn2 = c2b - c2a;
+    if (tid == 0) sm.ncn = (c1b - c1a) * cn2;
+    if (tid < (c1b - c1a) * cn2) {
+      const int ci = c1a + tid / cn2, cj = c2a + tid % cn2;
+      sm.cnw[tid] = ci * I->W2 + cj;
+      sm.cnt[tid] = (ci / I->G1) * I->TW2 + cj / I->G2;
+    }
   }
   __syncthreads();
-  int nn = 0;
-#pragma unroll
-  for (int q = 0; q < 9; ++q) nn += sh_nbr[q] >= 0;
-
-  unsigned long long my_upd = 0, my_cand = 0, my_lock = 0, my_visit = 0, my_chk = 0, my_patch = 0;
-  unsigned long long tk_wait = 0, tk_sel = 0, tk_col = 0, tk_app = 0, tk_mark = 0;
-  long long cursor = I.wstate ? I.wstate[2 * w] : 0;         // visits so far
-  int quiet = I.wstate ? (int)I.wstate[2 * w + 1] : 0;  // consecutive visits with no move >= tol and no patch of S_w
+  const int l = wave / wpl;  // this wave's worker within the team
+  const bool mine = l < gn, lead = mine && wave == l * wpl;
   const unsigned long long t_launch = __builtin_amdgcn_s_memrealtime();
-  int r = 0;
-  int exit_status = 0;
-  int next_exit = 0;  // thread 0: exit flags read at the end of the previous round
-  for (;; ++r) {
-    // ---- exit conditions
-    if (tid == 0) {
-      int f = r == 0 ? (ld_shared_i32(&I.ctl->converged) | ld_shared_i32(&I.ctl->stop)) : next_exit;
-      // every worker runs exactly max_rounds rounds: all moves of the last
-      // round are then applied everywhere and the launch can be resumed
-      if (!f && I.max_rounds > 0 && r >= I.max_rounds) {
-        atomicCAS(&I.ctl->status, 0, 1);
-        f = 1;
+  int r = 0, exit_status = 0;
+  bool leave = sm.exit_f != 0, capped = false;
+  __syncthreads();  // before exit_f is rewritten
+  for (; !leave; ++r) {
+    // ---- phase A
+    {
+      CInst<R> *const I = fresh<R>(I0);
+      // every team runs exactly max_rounds rounds: all moves of the last round
+      // are then applied everywhere and the launch can be resumed
+      if (I->max_rounds > 0 && r >= I->max_rounds) {
+        if (tid == 0) atomicCAS(&I->ctl->status, 0, 1);
+        capped = true;
+        break;
       }
-      if (!f && (long long)(__builtin_amdgcn_s_memrealtime() - t_launch) > I.budget_ticks) {
-        st_shared_i32(&I.ctl->stop, 1);
-        atomicCAS(&I.ctl->status, 0, 4);
-        f = 1;
-      }
-      sh_exit = f;
-      sh_cok = 1;
-      tk_mark = __builtin_amdgcn_s_memrealtime();
-    }
-    __syncthreads();
-    if (sh_exit) break;
-
-    // ---- phase A: `inner` visits.  Interior candidates are applied at once;
-    // the first band-reaching candidate is held for the protocol, and later
-    // interior candidates are applied only if neither lies in the other's
-    // V (they cannot interact); other candidates wait for the next cycle.
-    R bs = R(-1);
-    int bp = 0x7fffffff, bk = 0;
-    bool has = false;
-    int hh0 = 0, hw0 = 0;
-    long long restart = -1;  // first visit whose candidate had to wait: next round starts there
-    for (int v = 0; v < inner; ++v) {
-      const long long visit = cursor;
-      const int m = (int)(cursor % Mw);
-      ++cursor;
-      ++my_visit;
-      if (rnd) {
-        const unsigned long long u = sm64_draw(I.seed, (unsigned long long)w, (unsigned long long)visit);
-        const unsigned long long j = u % ((unsigned long long)npw * (unsigned long long)K);
-        const unsigned long long jp = j / (unsigned long long)K;
-        const int k = (int)(j - jp * (unsigned long long)K);
-        const int hh = a1 + (int)jp / ext2, ww = a2 + (int)jp % ext2;
-        const int pos = hh * W + ww;
-        if (tid == 0) {
-          const long long i0 = (long long)pos * I.KS + k;
-          const R zc = I.z[i0];
-          const R zn = st_target(I.beta[i0], I.lambda, sh_inv_n[k], I.positive);
-          sm.ck0 = k;
-          sm.czc = zc;
-          sm.czn = zn;
-          sh_rs[0] = move_score(zc, zn, I.tol, I.certify);
+      if (tid == 0) team_mark(sm, r, -1);
+      // Stopping consensus of the round before: one 64-bit counter per ring
+      // slot, completions in the low word and quiet workers in the high word.
+      // One thread adds its team's and reads the exit flags while the
+      // others select; the team acts on them in this round (a flag raised
+      // later only costs empty rounds).
+      unsigned long long ring_old = 0, ring_q = 0;
+      int flags = 0;
+      if (tid == kConsensus) {
+        if (r > 0) {
+          for (int q = 0; q < gn; ++q) ring_q += (unsigned)sm.done[q];
+          ring_old = __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(I->ring) + (r - 1) % kRing,
+                                            (unsigned long long)gn + (ring_q << 32), __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
         }
-        __syncthreads();
-        const R sc = sh_rs[0];
-        __syncthreads();
-        if (!(sc >= I.tol && sc > R(0))) continue;
-        quiet = 0;
-        ++my_cand;
-        has = true;
-        bs = sc;
-        bp = pos;
-        bk = k;
-        hh0 = hh;
-        hw0 = ww;
-        continue;
+        flags = ld_shared_i32(&I->ctl->converged) | ld_shared_i32(&I->ctl->stop);
       }
-      const int bi = m / nb2, bj = m - (m / nb2) * nb2;
-      const int s1 = a1 + part_start(bi, ext1, nb1), e1 = a1 + part_start(bi + 1, ext1, nb1);
-      const int s2 = a2 + part_start(bj, ext2, nb2), e2 = a2 + part_start(bj + 1, ext2, nb2);
-      const int bw = e2 - s2, np = (e1 - s1) * bw;
-      R vs = R(-1);
-      int vp = 0x7fffffff;
-      {
-        // four positions per pass with their loads in flight together; the
-        // (row, column) of position t steps by NT each time
-        const int dh = NT / bw, dw = NT - dh * bw;
-        int th = tid / bw, tw = tid - th * bw;
-        for (int t = tid; t < np; t += 4 * NT) {
-          R sc[4];
-          int ps[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            ps[u] = (s1 + th) * W + s2 + tw;
-            sc[u] = t + u * NT < np ? score_ld(I.score + ps[u]) : R(-1);
-            tw += dw;
-            th += dh;
-            if (tw >= bw) {
-              tw -= bw;
-              ++th;
+      const bool rnd = EXT && I->strategy == 3;
+      const int inner = !EXT || rnd ? 1 : (I->inner > 0 ? I->inner : 1);  // a worker makes at most Mw visits per round
+      const R tol = I->tol;
+      // the neighbouring teams' progress, read while the selection runs
+      const int *npr = nullptr;
+      int npg = 0x7fffffff;
+      if (lead && lane < 9) {
+        const int n = sm.nbt[lane];
+        if (n >= 0) {
+          npr = I->prog + n;
+          npg = ld_shared_i32(npr);
+        }
+      }
+      Held<R> c;
+      long long restart = -1;  // first visit whose candidate had to wait: the next round starts there
+      TeamWorker &k = sm.wk[mine ? l : 0];
+      for (int v = 0; v < inner; ++v) {
+        R vs = R(-1);
+        int vp = 0x7fffffff;
+        const int Mw = uni(k.nb1) * uni(k.nb2);
+        const bool on = mine && !rnd && (inner == 1 || v < Mw);
+        if (on) {
+          scan_visit<R, NT>(I, sm, ls, l, wave - l * wpl, wpl, vs, vp);
+          if (wpl > 1 && lane == 0) {
+            sm.ps[wave] = vs;
+            sm.pp[wave] = vp;
+          }
+        }
+        if (inner > 1 && lead && lane == 0) sm.ion[l] = 0;
+        if (wpl > 1 || inner > 1) __syncthreads();
+        if (lead && on) {
+          for (int q = 1; q < wpl; ++q) {
+            const R os = sm.ps[wave + q];
+            const int op = sm.pp[wave + q];
+            if (os > vs || (os == vs && op < vp)) {
+              vs = os;
+              vp = op;
             }
           }
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (sc[u] > vs || (sc[u] == vs && ps[u] < vp)) {
-              vs = sc[u];
-              vp = ps[u];
+          vp = uni(vp);
+          const bool hit = __any(vs >= tol && vs > R(0));
+          const long long visit = k.cursor;
+          if (hit) {
+            if (inner == 1) {
+              c.has = true;
+              c.bs = vs;
+              c.bp = vp;
+            } else {
+              visit_multi<R, NT>(I, sm, nzb, l, vs, vp, c, visit, restart);
             }
-        }
-      }
-      // with one visit per round each thread whose own best could be the
-      // candidate (a position of the sub-domain scoring >= tol) fetches its
-      // meta word while the block reduces, so the winning thread reads the
-      // candidate's z and beta one dependent load earlier
-      const int lp = vp;
-      const bool lok = inner == 1 && vs >= I.tol && vs > R(0);
-      const uint32_t lmeta = lok ? I.meta[lp] : 0u;
-      block_argmax<R, NT>(vs, vp, sh_rs, sh_ri);
-      if (!(vs >= I.tol && vs > R(0))) {
-        ++quiet;
-        continue;
-      }
-      quiet = 0;
-      ++my_cand;
-      const int h0 = vp / W, w0 = vp - (vp / W) * W;
-      // with one visit per round every candidate takes the published path, so
-      // its patch runs in phase B beside the neighbours' ones
-      const bool interior = inner > 1 && h0 >= in_lo1 && h0 < in_hi1 && w0 >= in_lo2 && w0 < in_hi2;
-      if (!interior) {
-        if (!has) {
-          has = true;
-          bs = vs;
-          bp = vp;
-          hh0 = h0;
-          hw0 = w0;
-          if (lok && lp == vp) {
-            const int k0 = meta_argk(lmeta);
-            const long long i0 = (long long)vp * I.KS + k0;
-            sm.ck0 = k0;
-            sm.cmeta = lmeta;
-            sm.czc = I.z[i0];
-            sm.czn = st_target(I.beta[i0], I.lambda, sh_inv_n[k0], I.positive);
           }
-        } else if (restart < 0) {
-          restart = visit;  // a second band-reaching candidate waits for the next round
+          if (lane == 0) {
+            k.cursor = visit + 1;
+            const int m = k.mcur + 1;
+            k.mcur = m == Mw ? 0 : m;
+            if (inner > 1) next_visit(k);
+            k.visit += 1;
+            k.cand += hit;
+            k.quiet = hit ? 0 : k.quiet + 1;
+          }
         }
-        continue;
-      }
-      if (has && abs(h0 - hh0) < I.L1 && abs(w0 - hw0) < I.L2) {  // would interact with the held one
-        if (restart < 0) restart = visit;
-        continue;
-      }
-      if (tid == 0) {
-        const int k0 = meta_argk(I.meta[vp]);
-        const long long i0 = (long long)vp * I.KS + k0;
-        const R zc = I.z[i0];
-        const R zn = st_target(I.beta[i0], I.lambda, sh_inv_n[k0], I.positive);
-        I.z[i0] = zn;
-        const uint32_t mt = I.meta[vp];
-        const int nzc = meta_nzc(mt) + (zn != R(0)) - (zc != R(0));
-        I.meta[vp] = meta_pack(meta_argk(mt), nzc);
-        if (P.nzb) nzb_put(P.nzb, (h0 - a1) * ext2 + (w0 - a2), nzc != 0);
-        UCand<R> &u = sm.ui;
-        u.k0 = k0;
-        u.ch = h0;
-        u.cw0 = w0;
-        u.r1 = max(h0 - I.L1 + 1, a1);
-        u.r2 = min(h0 + I.L1, b1);
-        u.c1 = max(w0 - I.L2 + 1, a2);
-        u.c2 = min(w0 + I.L2, b2);
-        u.aoff = ((k0 * I.U1 - h0 + I.L1 - 1) * I.U2 - w0 + I.L2 - 1) * I.KS;
-        u.delta = zn - zc;
-        if (I.div_guard > R(0) && (zn > I.div_guard || -zn > I.div_guard)) {
-          st_shared_i32(&I.ctl->stop, 1);
-          atomicCAS(&I.ctl->status, 0, 2);
+        if (inner > 1) {
+          // the interior candidates of this visit lie in different workers'
+          // blocks: their patches are disjoint
+          __syncthreads();
+          const PatchCtx<R> P = patch_ctx<R, NT>(I, sm, ls, nzb);
+          for (int q = 0; q < gn; ++q)
+            if (sm.ion[q])
+              patch_rect<R, NT, NG, false>(P, sm.ui + q, tid, sm.ui[q].r1, sm.ui[q].r2, sm.ui[q].c1, sm.ui[q].c2);
+          __syncthreads();
         }
+      }
+      if (lead) {
+        const int w = uni(k.w), a1 = uni(k.a1), b1 = uni(k.b1), a2 = uni(k.a2), b2 = uni(k.b2);
+        if (rnd) {
+          const unsigned npw = (unsigned)((b1 - a1) * (b2 - a2)), K = (unsigned)I->K;
+          const unsigned long long u = sm64_draw(I->seed, (unsigned long long)w, (unsigned long long)k.cursor);
+          const unsigned long long jd = u % ((unsigned long long)npw * K), jp = jd / K;
+          c.k0 = uni((int)(jd - jp * K));
+          c.bp = uni((a1 + (int)jp / (b2 - a2)) * I->W + a2 + (int)jp % (b2 - a2));
+          const long long i0 = (long long)c.bp * I->KS + c.k0;
+          c.zc = as_global((const R *)I->z)[i0];
+          c.zn = st_target((R)as_global((const R *)I->beta)[i0], (R)I->lambda, sm.inv_n[c.k0], I->positive);
+          c.bs = move_score(c.zc, c.zn, tol, I->certify);
+          c.has = __any(c.bs >= tol && c.bs > R(0));
+          if (lane == 0) {
+            k.cursor += 1;
+            k.visit += 1;
+            k.cand += c.has;
+            if (c.has) k.quiet = 0;
+          }
+        }
+        if (restart >= 0 && lane == 0) {
+          k.cursor = restart;
+          k.mcur = (int)(restart % (k.nb1 * k.nb2));
+          next_visit(k);
+        }
+        // The visits read only S_w, which this team alone writes and finished
+        // patching in its last phase B; so do the candidate's reads (its best
+        // atom, value and target).  Only the soft-lock test (the neighbours'
+        // scores of round r - 1) and the reuse of the candidate slot (read by
+        // the neighbours in round r - 1) need the neighbours' progress.
+        if (c.has && !rnd) best_move<R>(I, sm.inv_n, c.bp, &c.k0, &c.zc, &c.zn);
+        if (tid == 0) team_mark(sm, r, 1);
+        if (npg < r) {
+          const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+          while (ld_shared_i32(npr) < r) {
+            __builtin_amdgcn_s_sleep(1);
+            if ((long long)(__builtin_amdgcn_s_memrealtime() - t0) > timeout_ticks) {
+              sm.bad = 1;
+              break;
+            }
+          }
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (tid == 0) team_mark(sm, r, 0);
+        const int L1 = I->L1, L2 = I->L2, W = I->W;
+        const int h0 = c.has ? c.bp / W : 0, w0 = c.has ? c.bp - h0 * W : 0;
+        const bool test =
+            c.has && I->soft_lock && (h0 - L1 + 1 < a1 || h0 + L1 > b1 || w0 - L2 + 1 < a2 || w0 + L2 > b2);
+        if (test && lane == 0)
+          k.chk += (unsigned long long)(min(h0 + L1, I->H) - max(h0 - L1 + 1, 0)) *
+                   (unsigned long long)(min(w0 + L2, W) - max(w0 - L2 + 1, 0));
+        if (lane == 0) {
+          sm.cp[l] = test ? c.bp : -1;
+          sm.cs[l] = c.bs;
+          sm.clk[l] = 0;
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+      // V(w0) of more than 512 positions is read by the worker's whole group
+      const bool bigv = wpl > 1 && (long long)I->U1 * I->U2 > 512;
+      if (bigv) __syncthreads();
+      if (mine && (bigv || lead)) {
+        const int cp = uni(sm.cp[l]);
+        if (cp >= 0) {
+          const int ch = cp / I->W;
+          const bool lk = soft_test<R, NT>(I, sm, ls, uni(k.w), uni(k.a1), uni(k.b1), uni(k.a2), uni(k.b2), sm.cs[l],
+                                           ch, cp - ch * I->W, bigv ? wave - l * wpl : 0, bigv ? wpl : 1);
+          if (lk && lane == 0) sm.clk[l] = 1;
+        }
+      }
+      if (bigv) __syncthreads();
+      if (lead && lane == 0) {
+        // the band reads above are complete before the candidate becomes visible
         wait_vm();
-      }
-      __syncthreads();
-      ++my_upd;
-      my_patch += (unsigned long long)(sm.ui.r2 - sm.ui.r1) * (sm.ui.c2 - sm.ui.c1);
-      patch_union<R, NT>(I, P, &sm.ui, 1, sm.ui.r1, sm.ui.r2, sm.ui.c1, sm.ui.c2);
-    }
-    if (restart >= 0) cursor = restart;
-    int h0 = 0, w0 = 0;
-    if (has) {
-      h0 = bp / W;
-      w0 = bp - h0 * W;
-    }
-    // The visits above read only S_w, which this worker alone writes and
-    // finished patching in its last phase B; so do the candidate's reads
-    // (in the visit with one visit per round, below with several).  Only the soft-lock test (the neighbours' scores of round r - 1)
-    // and the reuse of the candidate slot (read by the neighbours in round
-    // r - 1) need the neighbours' progress.
-    if (tid == 0) {
-      if (has && inner != 1) {
-        const uint32_t mt = I.meta[bp];
-        const int k0 = meta_argk(mt);
-        const long long i0 = (long long)bp * I.KS + k0;
-        sm.ck0 = k0;
-        sm.cmeta = mt;
-        sm.czc = I.z[i0];
-        sm.czn = st_target(I.beta[i0], I.lambda, sh_inv_n[k0], I.positive);
-      }
-      const unsigned long long t = __builtin_amdgcn_s_memrealtime();
-      tk_sel += t - tk_mark;
-      tk_mark = t;
-    }
-    if (!wait_progress(I.prog, sh_nbr, nn, w, r, timeout_ticks, sm.wok)) {
-      exit_status = 3;
-      break;
-    }
-    if (tid == 0) {
-      const unsigned long long t = __builtin_amdgcn_s_memrealtime();
-      tk_wait += t - tk_mark;
-      tk_mark = t;
-    }
-    int locked = 0;
-    if (has && I.soft_lock &&
-        (h0 - I.L1 + 1 < a1 || h0 + I.L1 > b1 || w0 - I.L2 + 1 < a2 || w0 + I.L2 > b2)) {
-      // soft-lock test over V(w0), inside the valid domain, outside S_w
-      const int v1 = max(h0 - I.L1 + 1, 0), u1 = min(h0 + I.L1, H);
-      const int v2 = max(w0 - I.L2 + 1, 0), u2 = min(w0 + I.L2, W);
-      const int vw = u2 - v2, nv = (u1 - v1) * vw;
-      my_chk += nv;
-      int lk = 0;
-      {
-        const int dh = NT / vw, dw = NT - dh * vw;
-        int th = tid / vw, tw = tid - th * vw;
-        for (int t = tid; t < nv; t += 4 * NT) {
-          R sc[4];
-          int hq[4], wq[4];
-          bool use[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            hq[u] = v1 + th;
-            wq[u] = v2 + tw;
-            use[u] = t + u * NT < nv && !(hq[u] >= a1 && hq[u] < b1 && wq[u] >= a2 && wq[u] < b2);
-            sc[u] = use[u] ? score_ld(I.score + hq[u] * W + wq[u]) : R(-1);
-            tw += dw;
-            th += dh;
-            if (tw >= vw) {
-              tw -= vw;
-              ++th;
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            if (!use[u]) continue;
-            if (sc[u] > bs) {
-              lk = 1;
-            } else if (sc[u] == bs) {
-              const int owner = part_owner(hq[u], H, I.W1) * I.W2 + part_owner(wq[u], W, I.W2);
-              if (owner < w) lk = 1;
-            }
-          }
-        }
-      }
-      locked = block_or<NT>(lk, sh_ri);
-    }
-    // the band reads above are complete before the candidate becomes visible
-    wait_vm();
-    __syncthreads();
-    if (tid == 0) {
-      unsigned long long tag = cand_tag(r, 0, kNoPos);
-      unsigned long long dbits = 0;
-      if (has) {
-        if (locked) {
-          ++my_lock;
-        } else {
-          const int k0 = sm.ck0;
-          const long long i0 = (long long)bp * I.KS + k0;
-          const R zc = sm.czc;
-          const R zn = sm.czn;
+        const bool acc = c.has && !sm.clk[l];
+        const unsigned long long dbits = acc ? delta_bits<R>(c.zn - c.zc) : 0ull;
+        const unsigned long long rt = (unsigned long long)(unsigned)r << 32;
+        const int w = k.w;
+        unsigned long long *const cw = I->cand + (long long)kCandWords * w;
+        st_shared_u64(cw + 1, rt | (dbits & 0xffffffffull));
+        if (sizeof(R) == 8) st_shared_u64(cw + 2, rt | (dbits >> 32));
+        st_shared_u64(cw, acc ? cand_tag(r, c.k0, (unsigned)c.bp) : cand_tag(r, 0, kNoPos));
+        if (acc) {
           // z and its non-zero count change now; beta and the cache in phase B
-          I.z[i0] = zn;
-          // the meta word read with the candidate: nothing writes it since
-          const uint32_t mt = rnd ? I.meta[bp] : sm.cmeta;
-          const int nzc = meta_nzc(mt) + (zn != R(0)) - (zc != R(0));
-          I.meta[bp] = meta_pack(meta_argk(mt), nzc);
-          if (P.nzb) nzb_put(P.nzb, (h0 - a1) * ext2 + (w0 - a2), nzc != 0);
-          dbits = delta_bits<R>(zn - zc);
-          tag = cand_tag(r, k0, (unsigned)bp);
-          ++my_upd;
-          if (I.div_guard > R(0) && (zn > I.div_guard || -zn > I.div_guard)) {
-            st_shared_i32(&I.ctl->stop, 1);
-            atomicCAS(&I.ctl->status, 0, 2);
+          const int h0 = c.bp / I->W;
+          move_z<R, NT>(I, sm, nzb, c.bp, h0, c.bp - h0 * I->W, c.k0, c.zc, c.zn);
+          k.upd += 1;
+        } else if (c.has) {
+          k.lock += 1;
+        }
+        if (I->audit && r < I->audit_rounds)
+          I->audit[(long long)r * (I->W1 * I->W2) + w] = audit_record(c.has, acc, c.k0, c.bp);
+        next_visit(k);
+      }
+      if (tid == 0) team_mark(sm, r, 1);
+      if (tid == kConsensus) {
+        // the outcome of the stopping consensus
+        const unsigned long long nW = (unsigned long long)(I->W1 * I->W2);
+        if (r > 0 && (ring_old & 0xffffffffull) + (unsigned long long)gn == nW) {
+          st_shared_u64(reinterpret_cast<unsigned long long *>(I->ring) + (r - 1) % kRing, 0ull);
+          if ((ring_old >> 32) + ring_q == nW) {
+            st_shared_i32(&I->ctl->converged, 1);
+            flags = 1;
           }
         }
-      }
-      if (I.audit && r < I.audit_rounds)
-        I.audit[(long long)r * nW + w] = audit_record(has, has && !locked, sm.ck0, bp);
-      st_shared_u64(I.cand + 2 * w + 1, dbits);
-      wait_vm();
-      st_shared_u64(I.cand + 2 * w, tag);
-      const unsigned long long t = __builtin_amdgcn_s_memrealtime();
-      tk_sel += t - tk_mark;
-      tk_mark = t;
-    }
-
-    // ---- collect this round's candidates of the 3x3 neighbourhood; lane q
-    // also clips neighbour q's update to S_w for phase B
-    bool uval = false;
-    int uk0 = 0, uch = 0, ucw = 0, ur1 = 0, ur2 = 0, uc1 = 0, uc2 = 0;
-    R udl = R(0);
-    if (tid < nn) {
-      const int n = sh_nbr[tid];
-      unsigned long long t = 0;
-      int ok = 1;
-      const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-      const int rtag = r & ((1 << kRoundBits) - 1);
-      for (;;) {
-        // the tag and the progress word are read together, one round trip
-        // per poll
-        t = ld_shared_u64(I.cand + 2 * n);
-        const int pg = ld_shared_i32(I.prog + n);
-        if (tag_round(t) == rtag) break;
-        if (pg == 0x7fffffff) {
-          // the neighbour has left; it stored its last tag before its
-          // progress word, so a tag of this round is seen by a reread
-          t = ld_shared_u64(I.cand + 2 * n);
-          if (tag_round(t) != rtag) t = cand_tag(r, 0, kNoPos);
-          break;
+        if (!flags && (long long)(__builtin_amdgcn_s_memrealtime() - t_launch) > I->budget_ticks) {
+          st_shared_i32(&I->ctl->stop, 1);
+          atomicCAS(&I->ctl->status, 0, 4);
+          flags = 1;
         }
-        __builtin_amdgcn_s_sleep(1);
-        if ((long long)(__builtin_amdgcn_s_memrealtime() - t0) > timeout_ticks) {
-          ok = 0;
-          t = cand_tag(r, 0, kNoPos);
-          break;
-        }
-      }
-      const unsigned cpos = tag_pos(t);
-      if (cpos != kNoPos) {
-        udl = bits_delta<R>(ld_shared_u64(I.cand + 2 * n + 1));
-        uk0 = tag_k0(t);
-        uch = (int)(cpos / (unsigned)W);
-        ucw = (int)(cpos - (unsigned)uch * (unsigned)W);
-        ur1 = max(uch - I.L1 + 1, a1);
-        ur2 = min(uch + I.L1, b1);
-        uc1 = max(ucw - I.L2 + 1, a2);
-        uc2 = min(ucw + I.L2, b2);
-        uval = ur1 < ur2 && uc1 < uc2;
-      }
-      if (!ok) sh_cok = 0;
-    }
-    if (tid < 64) {
-      // the touching updates in neighbour order, their bounding box and the
-      // patched area, over the first wave's lanes
-      const unsigned long long bal = __ballot(uval);
-      if (uval) {
-        UCand<R> &u = sm.uc[__popcll(bal & ((1ull << tid) - 1ull))];
-        u.k0 = uk0;
-        u.ch = uch;
-        u.cw0 = ucw;
-        u.r1 = ur1;
-        u.r2 = ur2;
-        u.c1 = uc1;
-        u.c2 = uc2;
-        u.aoff = ((uk0 * I.U1 - uch + I.L1 - 1) * I.U2 - ucw + I.L2 - 1) * I.KS;
-        u.delta = udl;
-      }
-      int x1 = uval ? ur1 : b1, x2 = uval ? ur2 : a1, y1 = uval ? uc1 : b2, y2 = uval ? uc2 : a2;
-      unsigned pa = uval ? (unsigned)((ur2 - ur1) * (uc2 - uc1)) : 0u;
-#pragma unroll
-      for (int off = 8; off > 0; off >>= 1) {
-        x1 = min(x1, __shfl_xor(x1, off, 16));
-        x2 = max(x2, __shfl_xor(x2, off, 16));
-        y1 = min(y1, __shfl_xor(y1, off, 16));
-        y2 = max(y2, __shfl_xor(y2, off, 16));
-        pa += __shfl_xor(pa, off, 16);
-      }
-      if (tid == 0) {
-        const int nu = __popcll(bal);
-        sm.nuc = nu;
-        sm.ub[0] = x1;
-        sm.ub[1] = x2;
-        sm.ub[2] = y1;
-        sm.ub[3] = y2;
-        my_patch += pa;
-        // One pass over the bounding box pays for small patches, whose cost is
-        // mostly per-update latency (positions no update covers cost no loads).
-        // Large patches (over 1024 positions) are bandwidth-bound and go one by
-        // one: measured on 32x32 atoms (3969-position patches) the single pass
-        // costs 15-20% of the rounds' time.
-        sm.ub_union = nu > 1 && (long long)I.U1 * I.U2 <= 1024;
+        sm.exit_f = flags;
       }
     }
+    if (wave == kCollect) collect<R, NT>(fresh<R>(I0), sm, r, timeout_ticks);
     __syncthreads();
-    if (!sh_cok) {
+    if (tid == 0) team_mark(sm, r, 2);
+    if (sm.bad) {
       exit_status = 3;
       break;
     }
-    if (tid == 0) {
-      const unsigned long long t = __builtin_amdgcn_s_memrealtime();
-      tk_col += t - tk_mark;
-      tk_mark = t;
-    }
+    leave = sm.exit_f != 0;
 
-    // ---- phase B: apply the accepted candidates that touch S_w (eq. beta_update),
-    // all in one pass over the bounding box of their patches
-    if (sm.nuc > 0) {
-      quiet = 0;
-      if (sm.ub_union || sm.nuc == 1) {
-        patch_union<R, NT>(I, P, sm.uc, sm.nuc, sm.ub[0], sm.ub[1], sm.ub[2], sm.ub[3]);
+    // ---- phase B: apply the accepted candidates that touch the region (eq. beta_update)
+    const int nuc = uni(sm.nuc);
+    if (nuc > 0) {
+      CInst<R> *const I = fresh<R>(I0);
+      const PatchCtx<R> P = patch_ctx<R, NT>(I, sm, ls, nzb);
+      if (uni(sm.ub_union)) {
+        patch_union<R, NT, NG>(P, sm.uc, nuc, uni(sm.ub[0]), uni(sm.ub[1]), uni(sm.ub[2]), uni(sm.ub[3]));
       } else {
-        for (int c = 0; c < sm.nuc; ++c)
-          patch_union<R, NT>(I, P, sm.uc + c, 1, sm.uc[c].r1, sm.uc[c].r2, sm.uc[c].c1, sm.uc[c].c2);
+        // one after another; a barrier only before a patch that overlaps one
+        // since the last barrier, and each patch continues where the last
+        // left off in the order of the threads
+        int base = 0, rot = 0;
+        for (int c = 0; c < nuc; ++c) {
+          const UCand<R> &u = sm.uc[c];
+          if ((unsigned)uni((int)u.ov) >> base) {
+            __syncthreads();
+            base = c;
+          }
+          const int r1 = uni(u.r1), r2 = uni(u.r2), c1 = uni(u.c1), c2 = uni(u.c2);
+          patch_rect<R, NT, NG, false>(P, &u, (tid - rot) & (NT - 1), r1, r2, c1, c2);
+          rot = (rot + (((r2 - r1) * (c2 - c1)) << P.sh)) & (NT - 64);
+        }
+      }
+    }
+    const bool rnd = EXT && I0->strategy == 3;
+    if (lead) {
+      TeamWorker &k = sm.wk[l];
+      bool tch = false;
+      if (lane < nuc) {
+        const UCand<R> &u = sm.uc[lane];
+        tch = u.r1 < k.b1 && u.r2 > k.a1 && u.c1 < k.b2 && u.c2 > k.a2;
+      }
+      const int quiet = __any(tch) ? 0 : uni(k.quiet);
+      const int qthr = rnd ? 1 : uni(k.nb1) * uni(k.nb2);  // quiet count of a worker with no pending move
+      if (lane == 0) {
+        k.quiet = quiet;
+        sm.done[l] = quiet >= qthr ? 1 : 0;
       }
     }
     // cache stores complete before the progress counter moves
     wait_vm();
     __syncthreads();
-    if (rnd && cursor % npw == 0) {
-      // end of an epoch: the worker is quiet if no position of S_w holds a
-      // move scoring >= tol (every later patch of S_w clears it again)
-      R mx = R(-1);
-      int mp = 0;
-      for (int t = tid; t < npw; t += NT) {
-        const R sc = score_ld(I.score + (a1 + t / ext2) * W + a2 + t % ext2);
-        if (sc > mx) mx = sc;
-      }
-      block_argmax<R, NT>(mx, mp, sh_rs, sh_ri);
-      quiet = (mx >= I.tol && mx > R(0)) ? 0 : 1;
-    }
     if (tid == 0) {
-      st_shared_i32(I.prog + w, r + 1);
-      tk_app += __builtin_amdgcn_s_memrealtime() - tk_mark;
-      // ---- stopping consensus of round r: one 64-bit counter per ring slot,
-      // completions in the low word and quiet workers in the high word.  The
-      // exit flags for the next round are read while the add is in flight; a
-      // flag raised later in this round is seen one round later, which only
-      // costs an empty round.
-      const int slot = r % kRing;
-      unsigned long long *ring = reinterpret_cast<unsigned long long *>(I.ring);
-      const unsigned long long q = quiet >= qthr ? 1ull : 0ull;
-      const unsigned long long old =
-          __hip_atomic_fetch_add(&ring[slot], 1ull + (q << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      int f = ld_shared_i32(&I.ctl->converged) | ld_shared_i32(&I.ctl->stop);
-      if ((old & 0xffffffffull) == (unsigned long long)(nW - 1)) {
-        st_shared_u64(&ring[slot], 0ull);
-        if ((old >> 32) + q == (unsigned long long)nW) {
-          st_shared_i32(&I.ctl->converged, 1);
-          f = 1;
+      st_shared_i32(I0->prog + team, r + 1);
+      team_mark(sm, r, 3);
+    }
+    if (rnd) {
+      if (lead) {
+        CInst<R> *const I = fresh<R>(I0);
+        TeamWorker &k = sm.wk[l];
+        const int e2w = k.b2 - k.a2, npw = (k.b1 - k.a1) * e2w;
+        if (k.cursor % npw == 0) {
+          // end of an epoch: the worker is quiet if no position of S_w holds a
+          // move scoring >= tol (every later patch of S_w clears it again)
+          const GPtr<const R> sg = as_global((const R *)I->score);
+          R mx = R(-1);
+          for (int t = lane; t < npw; t += 64) {
+            const int h = k.a1 + t / e2w, w = k.a2 + t % e2w;
+            mx = fmax(mx, ls ? sm.score[(h - sm.A1) * (sm.B2 - sm.A2) + w - sm.A2] : sg[(long long)h * I->W + w]);
+          }
+          mx = wave_max(mx);
+          if (lane == 0) sm.done[l] = k.quiet = mx >= I->tol && mx > R(0) ? 0 : 1;
         }
       }
-      next_exit = f;
+      __syncthreads();
     }
   }
-  // ---- leave: neighbours must never wait on a finished worker
+  // ---- leave: neighbours must never wait on a finished team
   wait_vm();
   __syncthreads();
+  CInst<R> *const I = fresh<R>(I0);
+  Ctl *const ctl = I->ctl;
+  if (capped && r > 0 && tid == kConsensus) {  // the last round's consensus
+    const unsigned long long nW = (unsigned long long)(I->W1 * I->W2);
+    unsigned long long q = 0;
+    for (int i = 0; i < gn; ++i) q += (unsigned)sm.done[i];
+    const unsigned long long old =
+        __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(I->ring) + (r - 1) % kRing,
+                               (unsigned long long)gn + (q << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((old & 0xffffffffull) + (unsigned long long)gn == nW && (old >> 32) + q == nW)
+      st_shared_i32(&ctl->converged, 1);
+  }
+  if (tid < gn) {
+    const TeamWorker &k = sm.wk[tid];
+    atomicAdd(&ctl->n_updates, (unsigned long long)k.upd);
+    atomicAdd(&ctl->n_candidates, (unsigned long long)k.cand);
+    atomicAdd(&ctl->n_softlocked, (unsigned long long)k.lock);
+    atomicAdd(&ctl->n_visits, (unsigned long long)k.visit);
+    atomicAdd(&ctl->n_checked, k.chk);
+    atomicAdd(&ctl->n_patched, k.patch);
+    const int sweep = I->strategy == 3 ? (k.b1 - k.a1) * (k.b2 - k.a2) : k.nb1 * k.nb2;
+    atomicMax(&ctl->sweeps_done, (int)(k.cursor / sweep));
+    if (I->wstate) {
+      I->wstate[2 * k.w] = k.cursor;
+      I->wstate[2 * k.w + 1] = k.quiet;
+    }
+  }
   if (tid == 0) {
     if (exit_status) {
-      st_shared_i32(&I.ctl->stop, 1);
-      atomicCAS(&I.ctl->status, 0, exit_status);
+      st_shared_i32(&ctl->stop, 1);
+      atomicCAS(&ctl->status, 0, exit_status);
     }
-    atomicAdd(&I.ctl->n_updates, my_upd);
-    atomicAdd(&I.ctl->n_candidates, my_cand);
-    atomicAdd(&I.ctl->n_softlocked, my_lock);
-    atomicAdd(&I.ctl->n_visits, my_visit);
-    atomicAdd(&I.ctl->n_checked, my_chk);
-    atomicAdd(&I.ctl->n_patched, my_patch);
-    atomicAdd(&I.ctl->tk_wait, tk_wait);
-    atomicAdd(&I.ctl->tk_select, tk_sel);
-    atomicAdd(&I.ctl->tk_collect, tk_col);
-    atomicAdd(&I.ctl->tk_apply, tk_app);
-    atomicMax(&I.ctl->max_round, r);
-    atomicMax(&I.ctl->sweeps_done, (int)(cursor / (rnd ? npw : Mw)));
-    if (I.wstate) {
-      I.wstate[2 * w] = cursor;
-      I.wstate[2 * w + 1] = quiet;
-    }
-    st_shared_i32(I.prog + w, 0x7fffffff);
+    atomicAdd(&ctl->n_patched, sm.patched);
+    // the timed rounds stand for all, the team's phase times for those of each of its workers
+    const unsigned long long timed = (r + kTimed - 1) / kTimed;
+    for (int i = 0; i < 4; ++i) sm.tk[i] = timed ? sm.tk[i] * (unsigned long long)r / timed : 0;
+    atomicAdd(&ctl->tk_wait, sm.tk[0] * gn);
+    atomicAdd(&ctl->tk_select, sm.tk[1] * gn);
+    atomicAdd(&ctl->tk_collect, sm.tk[2] * gn);
+    atomicAdd(&ctl->tk_apply, sm.tk[3] * gn);
+    atomicMax(&ctl->max_round, r);
+    st_shared_i32(I->prog + team, 0x7fffffff);
   }
 }
 
-// Four 256-thread FP32 workers per CU (at most 128 VGPRs): the co-resident
-// worker count sets how finely an image can be split.
-template <class R, int NT> struct RoundWaves {
-  static constexpr int value = sizeof(R) == 4 ? (NT <= 256 ? NT / 64 : 4) : 1;
-};
-
-template <class R, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(RoundWaves<R, NT>::value))) void lgcd_rounds(const Inst<R> *__restrict__ insts,
-                                                   const int *__restrict__ wg_inst,
-                                                   long long timeout_ticks) {
-  __shared__ RoundSmem<R, NT> sm;
-  const int ii = wg_inst[blockIdx.x];
-  const Inst<R> I = insts[ii];
-  run_worker<R, NT>(I, blockIdx.x - I.wg_base, timeout_ticks, sm);
+// One 1024-thread team per CU, or four of 256 threads (at most 128 VGPRs).
+template <class R, int NT, int NG, bool EXT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void lgcd_rounds(
+    const Inst<R> *__restrict__ insts, const int *__restrict__ wg_inst, long long timeout_ticks) {
+  __shared__ TeamSmem<R, NT> sm;
+  CInst<R> *I = (CInst<R> *)(insts + wg_inst[blockIdx.x]);
+  run_team<R, NT, NG, EXT>(I, blockIdx.x - I->wg_base, timeout_ticks, sm);
 }
+
+// The kernel for positions of `ng` groups per lane (LaneMap::ng), with the
+// random rule and several visits per round if `ext`.  Defined per type and
+// workgroup size by rounds.hip.
+template <class R, int NT> const void *rounds_kernel(int ng, bool ext);
 
 }  // namespace dcdl

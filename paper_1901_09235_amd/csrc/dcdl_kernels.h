@@ -232,9 +232,9 @@ __global__ __launch_bounds__(256) void corr_kernel(Geom g, const Rin *__restrict
 }
 
 // ------------------------------------------------------- best-move cache
-// Best move of every position (the cache the round kernel keeps): score and
-// atom of the largest move score over the K atoms (lowest atom on ties), and
-// the position's count of non-zero coordinates.  A position's 16-byte atom
+// Best move of every position (the cache the round kernel keeps): the largest
+// move score over the K atoms, and the position's count of non-zero
+// coordinates.  A position's 16-byte atom
 // groups are read by a segment of S lanes (S the power of two covering them,
 // at most a wave), so a wave reads contiguous memory, and the segment reduces
 // with shuffles; each wave takes U groups of positions per step with all
@@ -259,11 +259,10 @@ __global__ __launch_bounds__(256) void init_moves(int HW, int K, int KS, const R
   const long long nwave = ((long long)gridDim.x * blockDim.x) >> 6;
   for (long long p0 = wave * per_wave * U; p0 < HW; p0 += nwave * per_wave * U) {
     R best[U];
-    int bk[U], nz[U];
+    int nz[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       best[u] = R(-1);
-      bk[u] = 0x7fffffff;
       nz[u] = 0;
     }
     for (int q = sl; q < G; q += S) {
@@ -287,10 +286,7 @@ __global__ __launch_bounds__(256) void init_moves(int HW, int K, int KS, const R
           const R zk = Vec<R>::get(zv[u], e);
           nz[u] += zk != R(0);
           const R sc = move_score(zk, st_target(Vec<R>::get(b[u], e), lambda, inv_n[k], positive), tol, certify);
-          if (sc > best[u] || (sc == best[u] && k < bk[u])) {
-            best[u] = sc;
-            bk[u] = k;
-          }
+          if (sc > best[u]) best[u] = sc;
         }
       }
     }
@@ -298,17 +294,13 @@ __global__ __launch_bounds__(256) void init_moves(int HW, int K, int KS, const R
     for (int u = 0; u < U; ++u) {
       for (int off = S >> 1; off > 0; off >>= 1) {
         const R ob = __shfl_xor(best[u], off, 64);
-        const int ok = __shfl_xor(bk[u], off, 64);
         nz[u] += __shfl_xor(nz[u], off, 64);
-        if (ob > best[u] || (ob == best[u] && ok < bk[u])) {
-          best[u] = ob;
-          bk[u] = ok;
-        }
+        if (ob > best[u]) best[u] = ob;
       }
       const long long pos = p0 + u * per_wave + seg;
       if (sl == 0 && pos < HW) {
         score[pos] = best[u];
-        meta[pos] = (uint32_t)bk[u] | ((uint32_t)nz[u] << 16);
+        meta[pos] = meta_pack(nz[u]);
       }
     }
   }
