@@ -288,6 +288,8 @@ int run_corr(hipStream_t stream, const Geom &g, const Rin *X, const Rin *D, cons
 int mf_of(int prec) { return prec == DCDL_CORR_F64 ? MF_F64 : (prec == DCDL_CORR_BF16 ? MF_BF16 : MF_BF16X3); }
 
 // ------------------------------------------------------------- FP64 by FFT
+constexpr long long kWholeRows = 1ll << 62;  // rows that no end of their input cuts
+
 // Transform sizes of the FFT contraction (dcdl_fft.h): images whose powers of
 // two covering T1 and T2 lie in [64, 8192] (a row transform fits the LDS), at
 // most 8 channels.
@@ -342,6 +344,12 @@ double mfma64_seconds(const Geom &g) {
   return 2.0 * 16 * ((g.K + 15) / 16) * g.P * g.L1 * g.L2 * (double)g.H * g.W / 55e12;
 }
 
+// The same for a signal's W positions, 256 per workgroup, on 256 CUs.
+double mfma64_signal_seconds(const Geom &g) {
+  const double blocks = (g.W + 255) / 256;
+  return mfma64_seconds(g) * std::max(1.0, 256.0 / blocks);
+}
+
 double fft64_seconds(const Geom &g, const FftGeom &f) {
   const double sp = 16.0 * f.plane, hw = (double)g.H * g.W;
   double b = (double)g.K * g.P * sp;                         // dictionary spectra (one write)
@@ -364,8 +372,137 @@ struct Fp64Ctx {
   int method = 0;
   bool dhat_ok = false;
   const void *dhat = nullptr;
+  const void *dhat1 = nullptr;  // the same for signals (slot "fft1_dhat"), null: not computed yet
   int n_fft = 0;
 };
+
+// The FFT contraction of signals: block length N2 of the row transforms (1024,
+// or 8192 where atoms are longer than 512), V valid outputs per block, nt
+// threads per row.
+struct Fft1Geom {
+  FftGeom f;
+  int V, nt;
+};
+
+bool fft1_geom(const Geom &g, Fft1Geom *o) {
+  if (g.T1 != 1 || g.L1 != 1 || g.L2 > 4096) return false;
+  const int N2 = g.L2 <= 512 ? 1024 : 8192;
+  o->f = FftGeom{};
+  o->f.N1 = 1;
+  o->f.N2 = N2;
+  o->f.M2 = N2 / 2;
+  o->f.F2p = (N2 / 2 + 1 + 15) / 16 * 16;
+  o->f.plane = o->f.F2p;
+  o->V = N2 - g.L2 + 1;
+  o->nt = N2 == 1024 ? 64 : kRowThreads;
+  return true;
+}
+
+// Estimated seconds: about 30 us of launches and the bytes its passes move at
+// 4 TB/s.  (K = 40 atoms of 32 x 128 taps, T = 134,001: 1.35 ms on the matrix
+// cores, whose FP64 rate bounds them.)
+double fft1_seconds(const Geom &g, const Fft1Geom &o) {
+  const double nb = (g.W + o.V - 1) / o.V, sp = 16.0 * o.f.F2p, P = g.P, K = g.K;
+  double b = 8.0 * P * g.T2 + sp * (2 * K * P + P * nb);                       // transforms of atoms and signal
+  b += sp * P * K * nb * (1.0 / (4 * kSpecK) + 1.0 / kSpecB) + 2 * sp * K * nb;  // products, inverse
+  b += 16.0 * K * g.W + 16.0 * g.KS * (double)g.W;                             // inverse, epilogue
+  return 30e-6 + b / 4e12;
+}
+
+// Whether an FP64 contraction of a signal goes by FFT under `method`: where it
+// is estimated faster than `other_s` seconds (0), never (1), always (2).
+bool fft1_pick(const Geom &g, int method, double other_s, Fft1Geom *o) {
+  if (method == 1 || !fft1_geom(g, o)) return false;
+  return method == 2 || fft1_seconds(g, *o) < other_s;
+}
+
+// Its workspace: signals are taken nbc blocks at a time, so that spectra and
+// outputs in flight stay within 1 GiB.
+struct Fft1Bufs {
+  double2 *tw = nullptr, *dhat = nullptr, *xhat = nullptr, *shat = nullptr;
+  double *G = nullptr;
+  int nbc = 0;
+};
+
+int fft1_chunk(const Geom &g, const Fft1Geom &o, long long W) {
+  const long long per = 16ll * o.f.F2p * (g.P + g.K) + 8ll * g.K * o.V, nb = (W + o.V - 1) / o.V;
+  return (int)std::max(1ll, std::min(nb, (1ll << 30) / per));
+}
+
+size_t fft1_dhat_bytes(const Geom &g, const Fft1Geom &o) { return 16 * (size_t)o.f.F2p * g.K * g.P; }
+
+// D64's spectra into b.dhat (and the twiddles into b.tw).
+int fft1_atoms(hipStream_t stream, const Geom &g, const Fft1Geom &o, const Fft1Bufs &b, const double *D64) {
+  hipLaunchKernelGGL(fft_twiddles, dim3(blocks_for(o.f.N2, 256)), dim3(256), 0, stream, o.f.N2, b.tw);
+  hipLaunchKernelGGL(fft_rows_r2c<double>, dim3(g.K * g.P), dim3(o.nt), sizeof(double2) * (size_t)o.f.M2, stream, o.f,
+                     D64, 0ll, g.L2, g.L2, kWholeRows, b.tw, b.dhat, 0ll);
+  HIPCK(hipGetLastError());
+  return DCDL_OK;
+}
+
+// The contraction corr(R64, D64) of a signal with the outputs of `o` in MODE
+// (as corr_mfma writes them), the atoms' spectra being in b.dhat.
+template <class Rz, int MODE>
+int corr_fft1(hipStream_t stream, const Geom &g, const Fft1Geom &f1, const Fft1Bufs &b, const double *R64,
+              const CorrOut &o) {
+  const FftGeom &f = f1.f;
+  const size_t lds = sizeof(double2) * (size_t)f.M2;
+  for (long long w0 = 0; w0 < g.W; w0 += (long long)b.nbc * f1.V) {
+    Geom gc = g;
+    gc.W = (int)std::min<long long>(g.W - w0, (long long)b.nbc * f1.V);
+    const int nb = (gc.W + f1.V - 1) / f1.V;
+    hipLaunchKernelGGL(fft_rows_r2c<double>, dim3(nb, g.P), dim3(f1.nt), lds, stream, f, R64 + w0, (long long)g.T2,
+                       f1.V, f.N2, (long long)g.T2 - w0, b.tw, b.xhat, (long long)nb * f.F2p);
+    hipLaunchKernelGGL(fft_spec_gemm, dim3((f.F2p + 63) / 64, (nb + kSpecB - 1) / kSpecB, (g.K + 4 * kSpecK - 1) / (4 * kSpecK)),
+                       dim3(256), 0, stream, g.K, g.P, nb, f.F2p, b.xhat, b.dhat, b.shat);
+    hipLaunchKernelGGL(fft_rows_c2r, dim3(nb, g.K), dim3(f1.nt), lds, stream, f, b.shat, (long long)nb * f.F2p, b.tw,
+                       b.G, (long long)gc.W, f1.V, (long long)gc.W, 1.0 / f.M2);
+    CorrOut oc = o;
+    const long long e = w0 * g.KS;
+    if (oc.beta) oc.beta = (char *)oc.beta + sizeof(Rz) * e;
+    if (oc.zpm) oc.zpm = (const char *)oc.zpm + sizeof(Rz) * e;
+    if (oc.beta_cmp) oc.beta_cmp = (const char *)oc.beta_cmp + sizeof(Rz) * e;
+    if (oc.g64) oc.g64 += e;
+    if (oc.meta) oc.meta += w0;
+    hipLaunchKernelGGL((fft_epilogue<MODE, Rz>), dim3((unsigned)std::min((gc.W + 63) / 64, 4096)), dim3(256), 0, stream,
+                       gc, b.G, oc);
+  }
+  HIPCK(hipGetLastError());
+  return DCDL_OK;
+}
+
+// corr_fft1's workspace from the device's slots, and the atoms' spectra unless
+// ctx says that they are there; *fits = false where memory does not.
+int fft1_prepare(DeviceState *ds, hipStream_t stream, const Geom &g, const Fft1Geom &f1, const double *D64,
+                 Fp64Ctx *ctx, Fft1Bufs *b, bool *fits) {
+  b->nbc = fft1_chunk(g, f1, g.W);
+  const size_t sp = 16 * (size_t)f1.f.F2p * b->nbc;
+  const struct {
+    const char *name;
+    size_t bytes;
+    void **p;
+  } slots[] = {{"fft1_tw", 16 * (size_t)f1.f.N2, (void **)&b->tw},
+               {"fft1_dhat", fft1_dhat_bytes(g, f1), (void **)&b->dhat},
+               {"fft1_xhat", sp * g.P, (void **)&b->xhat},
+               {"fft1_shat", sp * g.K, (void **)&b->shat},
+               {"fft1_g", 8 * (size_t)g.K * b->nbc * f1.V, (void **)&b->G}};
+  *fits = true;
+  for (const auto &s : slots) {
+    const int rc = ws_get(ds, stream, s.name, s.bytes, s.p);
+    if (rc == DCDL_ENOMEM) {
+      g_err.clear();
+      *fits = false;
+      return DCDL_OK;
+    }
+    if (rc) return rc;
+  }
+  if (ctx->dhat1 != b->dhat) {
+    const int rc = fft1_atoms(stream, g, f1, *b, D64);
+    if (rc) return rc;
+    ctx->dhat1 = b->dhat;
+  }
+  return DCDL_OK;
+}
 
 // Whether an FP64 contraction of g runs by FFT under `method`, and the atom
 // chunk of its inverse transforms (the workspace is kept within 60% of the
@@ -451,14 +588,14 @@ int corr_fft64(DeviceState *ds, hipStream_t stream, const Geom &g, const FftGeom
   if (!ctx || !ctx->dhat_ok || ctx->dhat != dhat) {
     if (E) {
       hipLaunchKernelGGL(fft_rows_r2c<double>, dim3(g.L1, KP), dim3(kRowThreads), lds_row, stream, f, D64,
-                         (long long)g.L1 * g.L2, g.L2, g.L2, tw2, E, (long long)g.L1 * f.F2p);
+                         (long long)g.L1 * g.L2, g.L2, g.L2, kWholeRows, tw2, E, (long long)g.L1 * f.F2p);
       if (f.B > 1)
         fft_cols_m(f.B, stream, f, dhat, KP, f.A, f.B, 1, f.N1, f.N1, 0, 0, tw1, E, (long long)g.L1 * f.F2p, g.L1);
       else
         fft_cols_m(f.N1, stream, f, dhat, KP, 1, 0, 1, f.N1, f.N1, 0, 0, tw1, E, (long long)g.L1 * f.F2p, g.L1);
     } else {
       hipLaunchKernelGGL(fft_rows_r2c<double>, dim3(g.L1, KP), dim3(kRowThreads), lds_row, stream, f, D64,
-                         (long long)g.L1 * g.L2, g.L2, g.L2, tw2, dhat, f.plane);
+                         (long long)g.L1 * g.L2, g.L2, g.L2, kWholeRows, tw2, dhat, f.plane);
       fft_cols_forward(stream, f, dhat, KP, g.L1, tw1);
     }
     if (ctx) {
@@ -467,7 +604,7 @@ int corr_fft64(DeviceState *ds, hipStream_t stream, const Geom &g, const FftGeom
     }
   }
   hipLaunchKernelGGL(fft_rows_r2c<double>, dim3(g.T1, g.P), dim3(kRowThreads), lds_row, stream, f, R64,
-                     (long long)g.T1 * g.T2, g.T2, g.T2, tw2, rhat, f.plane);
+                     (long long)g.T1 * g.T2, g.T2, g.T2, kWholeRows, tw2, rhat, f.plane);
   fft_cols_forward(stream, f, rhat, g.P, g.T1, tw1);
   const long long HW = (long long)g.H * g.W;
   const double scale = 1.0 / ((double)f.N1 * f.M2);
@@ -504,7 +641,7 @@ int corr_fft64(DeviceState *ds, hipStream_t stream, const Geom &g, const FftGeom
       fft_cols_inverse(stream, f, shat, nk, g.H, tw1);
     }
     hipLaunchKernelGGL(fft_rows_c2r, dim3(g.H, nk), dim3(kRowThreads), lds_row, stream, f, shat, f.plane, tw2,
-                       G + (long long)k0 * HW, HW, g.W, scale);
+                       G + (long long)k0 * HW, HW, g.W, kWholeRows, scale);
   }
   const unsigned nb = (unsigned)std::min<long long>((HW + 63) / 64, 4096);
   hipLaunchKernelGGL((fft_epilogue<MODE, Rz>), dim3(nb), dim3(256), 0, stream, g, G, o);
@@ -561,11 +698,41 @@ int run_dtd_mfma(hipStream_t stream, const Geom &g, const Geom &gi, const R *D, 
   return DCDL_OK;
 }
 
+// With ctx (not in the fixed scratch), atoms of signals for which the FFT is
+// estimated faster take it: the DtD image is a signal of K (2L - 1) positions,
+// too short to fill the CUs on the matrix cores (40 atoms of 32 x 128 taps:
+// 580 us, 40 workgroups).  D in FP64 is left in the "D64" slot.
 template <class R>
-int run_dtd(DeviceState *ds, hipStream_t stream, const Geom &g, const R *D, R *dtd, R *A, R *inv_n) {
+int run_dtd(DeviceState *ds, hipStream_t stream, const Geom &g, const R *D, R *dtd, R *A, R *inv_n,
+            Fp64Ctx *ctx = nullptr) {
   Geom gi;
-  if (!dtd_geom(g, &gi)) return run_dtd_loops<R>(stream, g, D, dtd, A, inv_n);
+  const bool mfma = dtd_geom(g, &gi);
   void *ws;
+  Fft1Geom f1;
+  if (ctx && mfma && !ds->arena && fft1_pick(gi, ctx->method, mfma64_signal_seconds(gi), &f1)) {
+    const long long nd = (long long)g.K * g.P * g.L2, nimg = (long long)gi.P * gi.T2;
+    double *D64;
+    WS("D64", sizeof(double) * nd, D64);
+    hipLaunchKernelGGL((convert_kernel<R, double>), dim3(grid_stride_blocks(nd)), dim3(256), 0, stream, nd, D, D64);
+    Fft1Bufs b;
+    bool fits = false;
+    int rc = fft1_prepare(ds, stream, gi, f1, D64, ctx, &b, &fits);
+    if (rc) return rc;
+    if (fits) {
+      WS("dtd_ws", dtd_ws_bytes(gi).total(), ws);
+      const DtdWs w = dtd_ws_bytes(gi);
+      double *img = (double *)ws, *G = (double *)((char *)ws + w.img + w.pk);
+      hipLaunchKernelGGL(dtd_image<R>, dim3(grid_stride_blocks(nimg)), dim3(256), 0, stream, gi, D, img, nimg);
+      CorrOut o{};
+      o.beta = G;
+      if ((rc = corr_fft1<double, CORR_BETA>(stream, gi, f1, b, img, o))) return rc;
+      const long long n = (long long)g.K * g.U2 * g.K;
+      hipLaunchKernelGGL(dtd_gather<R>, dim3(grid_stride_blocks(n)), dim3(256), 0, stream, g, G, dtd, A, inv_n, n);
+      HIPCK(hipGetLastError());
+      return DCDL_OK;
+    }
+  }
+  if (!mfma) return run_dtd_loops<R>(stream, g, D, dtd, A, inv_n);
   WS("dtd_ws", dtd_ws_bytes(gi).total(), ws);
   return run_dtd_mfma<R>(stream, g, gi, D, dtd, A, inv_n, ws);
 }
@@ -692,6 +859,17 @@ int corr64x(DeviceState *ds, hipStream_t stream, const Geom &g, const double *R6
   if (ctx && fft64_pick(ds, g, ctx->method, &f, &kc)) {
     ++ctx->n_fft;
     return corr_fft64<Rz, MODE>(ds, stream, g, f, kc, R64, D64, o, ctx);
+  }
+  Fft1Geom f1;
+  if (ctx && !ds->arena && fft1_pick(g, ctx->method, mfma64_signal_seconds(g), &f1)) {
+    Fft1Bufs b;
+    bool fits = false;
+    int rc = fft1_prepare(ds, stream, g, f1, D64, ctx, &b, &fits);
+    if (rc) return rc;
+    if (fits) {
+      ++ctx->n_fft;
+      return corr_fft1<Rz, MODE>(stream, g, f1, b, R64, o);
+    }
   }
   return corr64<Rz, MODE>(stream, g, R64, D64, pk64, o);
 }
@@ -1103,14 +1281,14 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
   HIPCK(hipEventRecord(ev0, stream));
   if (g.KS != g.K) HIPCK(hipMemsetAsync(A, 0, sizeof(R) * nA, stream));  // padding atoms patch nothing
   HIPCK(hipMemsetAsync(inv_n, 0, sizeof(R) * g.KS, stream));
-  if ((rc = run_dtd<R>(ds, stream, g, D, dtd, A, inv_n))) return rc;
+  // the solve's FP64 contractions (and the DtD table of a signal) share one
+  // set of dictionary spectra when they run by FFT
+  Fp64Ctx f64;
+  f64.method = o->fp64_method;
+  if ((rc = run_dtd<R>(ds, stream, g, D, dtd, A, inv_n, &f64))) return rc;
   hipLaunchKernelGGL(norms64<R>, dim3(g.K), dim3(256), 0, stream, g.K, g.P * g.L1 * g.L2, D, nrm64);
   CorrTimer tm_init(evs.e[3], evs.e[4]), tm64(evs.e[5], evs.e[6]);
   int init_prec = DCDL_CORR_F64;
-  // the solve's FP64 contractions share one set of dictionary spectra when
-  // they run by FFT
-  Fp64Ctx f64;
-  f64.method = o->fp64_method;
   if (o->warm_start) {
     launch_to_position_major<R, R>(stream, HW, g.K, g.KS, z_out, zpm);
     if ((rc = beta_from_z64<R>(ds, stream, g, X, D, zpm, nrm64, beta, true, &tm64, nullptr, &f64))) return rc;
@@ -1172,7 +1350,9 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
   // The dense FP64 contraction: by FFT or on the matrix cores (fp64_method).
   FftGeom fgeom;
   int fkc = 0;
-  const bool dense_fft = fft64_pick(ds, g, f64.method, &fgeom, &fkc);
+  Fft1Geom f1geom;
+  const bool dense_fft1 = !ds->arena && fft1_pick(g, f64.method, mfma64_signal_seconds(g), &f1geom);
+  const bool dense_fft = dense_fft1 || fft64_pick(ds, g, f64.method, &fgeom, &fkc);
   // FP64 reference of the incremental check: g and z of the last dense FP64
   // contraction (its residual stays in the "res64" slot).  Used with the
   // matrix-core contraction only: the FFT contraction costs less than
@@ -1187,7 +1367,9 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
   // K (2L1-1)(2L2-1) FP64 table entries each, cost under half the dense
   // contraction's 2 (16 ceil(K/16)) P L1 L2 flops per position (rates of the
   // two paths on gfx950: about 6 TB/s of table reads, 55 TFLOP/s of FP64 MFMA)
-  const double dense_s = dense_fft ? fft64_seconds(g, fgeom) : mfma64_seconds(g);
+  const double dense_s = dense_fft1  ? fft1_seconds(g, f1geom)
+                         : dense_fft ? fft64_seconds(g, fgeom)
+                                     : mfma64_seconds(g);
   const long long max_changes = std::max(1ll, std::min((long long)(0.5 * dense_s * 6e12 / (8.0 * g.K * g.U1 * g.U2)),
                                                        HW * g.K));
   CorrTimer tm_inc(evs.e[3], evs.e[4]);
@@ -1558,12 +1740,14 @@ int dicodile_dtd(const dcdl_shape *shape, dcdl_dtype dtype, const void *D, void 
     float *A, *inv;
     WS("applyA", sizeof(float) * nA, A);
     WS("inv_n", sizeof(float) * g.K, inv);
-    if ((rc = run_dtd<float>(ds, stream, g, (const float *)D, (float *)dtd_out, A, inv))) return rc;
+    Fp64Ctx ctx;
+    if ((rc = run_dtd<float>(ds, stream, g, (const float *)D, (float *)dtd_out, A, inv, &ctx))) return rc;
   } else if (dtype == DCDL_F64) {
     double *A, *inv;
     WS("applyA", sizeof(double) * nA, A);
     WS("inv_n", sizeof(double) * g.K, inv);
-    if ((rc = run_dtd<double>(ds, stream, g, (const double *)D, (double *)dtd_out, A, inv))) return rc;
+    Fp64Ctx ctx;
+    if ((rc = run_dtd<double>(ds, stream, g, (const double *)D, (double *)dtd_out, A, inv, &ctx))) return rc;
   } else {
     return fail(DCDL_EINVAL, "unknown dtype %d", (int)dtype);
   }

@@ -1,4 +1,9 @@
-// dcdl_fft.h -- the dense FP64 correlation G = corr(R, D) of an image by FFT.
+// dcdl_fft.h -- the dense FP64 correlation G = corr(R, D) by FFT.
+//
+// Signals go by overlap-save: blocks of N2 samples that start V = N2 - L + 1
+// apart, a row transform each, a complex matrix product per frequency
+// (fft_spec_gemm) and inverse row transforms cropped to the block's V valid
+// outputs.  Images:
 //
 // G_k = sum_p corr(R_p, D_kp) on the valid domain (the contraction behind beta
 // = corr(X - Z*D, D) + n z of Sec. 3 and the optimality check of eq. csc) is,
@@ -192,15 +197,18 @@ __device__ void lds_fft(double2 *a, int n, const double2 *__restrict__ tw, int t
 }
 
 // One row per workgroup (blockIdx.x), one input per blockIdx.y: the half
-// spectrum X[0 .. M2] of the real row x (zero beyond `cols`), written with
-// zero padding up to F2p.  LDS: M2 complex values.
+// spectrum X[0 .. M2] of the real row x (zero beyond `cols`, and beyond the
+// `total` values an input holds from its first row on), written with zero
+// padding up to F2p.  LDS: M2 complex values.  At least M2 / 8 threads where M2
+// is a power of 8, else kRowThreads.
 template <class Rin>
 __global__ __launch_bounds__(kRowThreads) void fft_rows_r2c(FftGeom f, const Rin *__restrict__ x, long long xb, int xp,
-                                                    int cols, const double2 *__restrict__ tw2,
+                                                    int cols, long long total, const double2 *__restrict__ tw2,
                                                     double2 *__restrict__ out, long long ob) {
   extern __shared__ double2 fsm[];
   double2 *a = fsm;
   const Rin *xr = x + blockIdx.y * xb + (long long)blockIdx.x * xp;
+  cols = (int)min((long long)cols, total - (long long)blockIdx.x * xp);
   for (int n = threadIdx.x; n < f.M2; n += blockDim.x) {
     const int c0 = 2 * n, c1 = 2 * n + 1;
     a[n] = make_double2(c0 < cols ? (double)xr[c0] : 0.0, c1 < cols ? (double)xr[c1] : 0.0);
@@ -224,10 +232,11 @@ __global__ __launch_bounds__(kRowThreads) void fft_rows_r2c(FftGeom f, const Rin
 
 // One output row h < H per workgroup (blockIdx.x), one spectrum per
 // blockIdx.y: the real row whose half spectrum is row h of S, times `scale`,
-// written for columns < W into G (row pitch W, batch stride gb).
+// written for columns < W into G (row pitch W, batch stride gb, of whose
+// `total` values none beyond is written).
 __global__ __launch_bounds__(kRowThreads) void fft_rows_c2r(FftGeom f, const double2 *__restrict__ S, long long sb,
                                                     const double2 *__restrict__ tw2, double *__restrict__ G,
-                                                    long long gb, int W, double scale) {
+                                                    long long gb, int W, long long total, double scale) {
   extern __shared__ double2 fsm[];
   double2 *a = fsm;
   const double2 *X = S + blockIdx.y * sb + (long long)blockIdx.x * f.F2p;
@@ -251,6 +260,7 @@ __global__ __launch_bounds__(kRowThreads) void fft_rows_c2r(FftGeom f, const dou
   lds_fft(a, f.M2, tw2, 2, true);
   const double2 *z = a;
   double *g = G + blockIdx.y * gb + (long long)blockIdx.x * W;
+  W = (int)min((long long)W, total - (long long)blockIdx.x * W);
   for (int n = threadIdx.x; n < f.M2; n += blockDim.x) {
     const int c0 = 2 * n, c1 = 2 * n + 1;
     if (c0 < W) g[c0] = z[n].x * scale;
@@ -437,6 +447,46 @@ __global__ __launch_bounds__(256) void fft_product(long long plane, int P, int k
       Sh[kk * plane + e] = acc;
     }
   }
+}
+
+// Signals: Sh[k][b] = sum_p Xh[p][b] conj(Dh[k][p]) over spectra of pitch F2p of
+// nb blocks of the signal, K atoms and P channels: a small complex matrix
+// product per frequency.  A lane holds one frequency of a tile of KT atoms x BT
+// blocks, so a read of either serves the whole other side of the tile; the
+// four waves of a workgroup take neighbouring atoms and share the signal's
+// reads through the L1.  The reads (all of them contiguous over the lanes)
+// bound it: 16 (K / KT + nb / BT) P F2p bytes each way past the registers.
+constexpr int kSpecK = 4, kSpecB = 8;
+__global__ __launch_bounds__(256) void fft_spec_gemm(int K, int P, int nb, int F2p, const double2 *__restrict__ Xh,
+                                                     const double2 *__restrict__ Dh, double2 *__restrict__ Sh) {
+  const int f = blockIdx.x * 64 + (threadIdx.x & 63);
+  const int k0 = (blockIdx.z * 4 + (threadIdx.x >> 6)) * kSpecK, b0 = blockIdx.y * kSpecB;
+  if (f >= F2p || k0 >= K) return;
+  double2 acc[kSpecK][kSpecB];
+#pragma unroll
+  for (int i = 0; i < kSpecK; ++i)
+#pragma unroll
+    for (int j = 0; j < kSpecB; ++j) acc[i][j] = make_double2(0.0, 0.0);
+  // past the last atom or block the last one is read again and not written
+  for (int p = 0; p < P; ++p) {
+    double2 d[kSpecK], x[kSpecB];
+#pragma unroll
+    for (int i = 0; i < kSpecK; ++i) d[i] = Dh[((long long)min(k0 + i, K - 1) * P + p) * F2p + f];
+#pragma unroll
+    for (int j = 0; j < kSpecB; ++j) x[j] = Xh[((long long)p * nb + min(b0 + j, nb - 1)) * F2p + f];
+#pragma unroll
+    for (int i = 0; i < kSpecK; ++i)
+#pragma unroll
+      for (int j = 0; j < kSpecB; ++j) {
+        acc[i][j].x += x[j].x * d[i].x + x[j].y * d[i].y;
+        acc[i][j].y += x[j].y * d[i].x - x[j].x * d[i].y;
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < kSpecK; ++i)
+#pragma unroll
+    for (int j = 0; j < kSpecB; ++j)
+      if (k0 + i < K && b0 + j < nb) Sh[((long long)(k0 + i) * nb + b0 + j) * F2p + f] = acc[i][j];
 }
 
 // The contraction's outputs from G (K, H, W) in FP64, as corr_mfma's epilogue
