@@ -1098,17 +1098,10 @@ __device__ __forceinline__ void collect(CInst<R> *I, TeamSmem<R, NT> &sm, int r,
     u.delta = udl;
   }
   __builtin_amdgcn_wave_barrier();
-  // bounding box and area of the patches, over the lanes (at most 32 workers)
-  int x1 = uval ? ur1 : B1, x2 = uval ? ur2 : A1, y1 = uval ? uc1 : B2, y2 = uval ? uc2 : A2;
-  unsigned pa = uval ? (unsigned)((ur2 - ur1) * (uc2 - uc1)) : 0u;
-#pragma unroll
-  for (int off = 16; off > 0; off >>= 1) {
-    x1 = min(x1, __shfl_xor(x1, off, 32));
-    x2 = max(x2, __shfl_xor(x2, off, 32));
-    y1 = min(y1, __shfl_xor(y1, off, 32));
-    y2 = max(y2, __shfl_xor(y2, off, 32));
-    pa += __shfl_xor(pa, off, 32);
-  }
+  // bounding box and area of the patches
+  if (uval) atomicAdd(&sm.patched, (unsigned long long)((ur2 - ur1) * (uc2 - uc1)));
+  const int x1 = wave_min(uval ? ur1 : B1), x2 = -wave_min(uval ? -ur2 : -A1);
+  const int y1 = wave_min(uval ? uc1 : B2), y2 = -wave_min(uval ? -uc2 : -A2);
   // One pass over the bounding box pays for small patches, whose cost is
   // mostly per-update latency (positions no update covers cost no loads).
   // Large patches (over 1024 positions) are bandwidth-bound and go one by
@@ -1130,7 +1123,6 @@ __device__ __forceinline__ void collect(CInst<R> *I, TeamSmem<R, NT> &sm, int r,
     sm.ub[1] = x2;
     sm.ub[2] = y1;
     sm.ub[3] = y2;
-    sm.patched += pa;
     sm.ub_union = un;
   }
 }
@@ -1188,11 +1180,16 @@ __device__ __forceinline__ void run_team(CInst<R> *const I0, const int team, con
     nzb = nreg <= 32 * kNzWords;
     // Each worker has a group of wpl waves, the first of which leads (selects,
     // tests, publishes).  One wave reads up to 512 positions of a sub-domain or
-    // of a V(w0); larger ones get more waves while they last.
+    // of a V(w0); larger ones share half of the workgroup's waves, or all of
+    // them where a wave would still read over 1024 (the others collect and keep
+    // the consensus meanwhile: 1024^2 image, 1024 positions, 195 ms of rounds
+    // with all of them and 191 with half; 4096^2 RGB image, 4096 positions,
+    // 11.4 us per selection and 16.1).
     const long long tp = max((long long)min(I->tile1, H) * min(I->tile2, W), (long long)I->U1 * I->U2);
     int gp = 1;
     while (gp < gn) gp <<= 1;
-    while (wpl * 2 * gp <= NW && (long long)wpl * 512 < tp) wpl <<= 1;
+    if (tp > 512)
+      while (wpl * 4 * gp <= NW || (wpl * 2 * gp <= NW && (long long)wpl * 1024 < tp)) wpl <<= 1;
     if (tid < gn) {
       TeamWorker &k = sm.wk[tid];
       const int wi = w1a + tid / g2, wj = w2a + tid % g2;
@@ -1296,6 +1293,9 @@ __device__ __forceinline__ void run_team(CInst<R> *const I0, const int team, con
           npg = ld_shared_i32(npr);
         }
       }
+      // V(w0) of more than 512 positions is read by the worker's whole group
+      const bool bigv = wpl > 1 && (long long)I->U1 * I->U2 > 512;
+      int locked = 0;
       Held<R> c;
       long long restart = -1;  // first visit whose candidate had to wait: the next round starts there
       TeamWorker &k = sm.wk[mine ? l : 0];
@@ -1314,13 +1314,10 @@ __device__ __forceinline__ void run_team(CInst<R> *const I0, const int team, con
         if (inner > 1 && lead && lane == 0) sm.ion[l] = 0;
         if (wpl > 1 || inner > 1) __syncthreads();
         if (lead && on) {
-          for (int q = 1; q < wpl; ++q) {
-            const R os = sm.ps[wave + q];
-            const int op = sm.pp[wave + q];
-            if (os > vs || (os == vs && op < vp)) {
-              vs = os;
-              vp = op;
-            }
+          if (wpl > 1) {
+            vs = lane < wpl ? sm.ps[wave + lane] : R(-1);
+            vp = lane < wpl ? sm.pp[wave + lane] : 0x7fffffff;
+            wave_argmax(vs, vp);
           }
           vp = uni(vp);
           const bool hit = __any(vs >= tol && vs > R(0));
@@ -1406,30 +1403,32 @@ __device__ __forceinline__ void run_team(CInst<R> *const I0, const int team, con
         if (test && lane == 0)
           k.chk += (unsigned long long)(min(h0 + L1, I->H) - max(h0 - L1 + 1, 0)) *
                    (unsigned long long)(min(w0 + L2, W) - max(w0 - L2 + 1, 0));
-        if (lane == 0) {
-          sm.cp[l] = test ? c.bp : -1;
-          sm.cs[l] = c.bs;
-          sm.clk[l] = 0;
+        if (bigv) {
+          if (lane == 0) {
+            sm.cp[l] = test ? c.bp : -1;
+            sm.cs[l] = c.bs;
+            sm.clk[l] = 0;
+          }
+        } else if (test) {
+          locked = soft_test<R, NT>(I, sm, ls, w, a1, b1, a2, b2, c.bs, h0, w0, 0, 1);
         }
-        __builtin_amdgcn_wave_barrier();
       }
-      // V(w0) of more than 512 positions is read by the worker's whole group
-      const bool bigv = wpl > 1 && (long long)I->U1 * I->U2 > 512;
-      if (bigv) __syncthreads();
-      if (mine && (bigv || lead)) {
-        const int cp = uni(sm.cp[l]);
+      if (bigv) {
+        __syncthreads();
+        const int cp = mine ? uni(sm.cp[l]) : -1;
         if (cp >= 0) {
           const int ch = cp / I->W;
           const bool lk = soft_test<R, NT>(I, sm, ls, uni(k.w), uni(k.a1), uni(k.b1), uni(k.a2), uni(k.b2), sm.cs[l],
-                                           ch, cp - ch * I->W, bigv ? wave - l * wpl : 0, bigv ? wpl : 1);
+                                           ch, cp - ch * I->W, wave - l * wpl, wpl);
           if (lk && lane == 0) sm.clk[l] = 1;
         }
+        __syncthreads();
+        if (lead) locked = sm.clk[l];
       }
-      if (bigv) __syncthreads();
       if (lead && lane == 0) {
         // the band reads above are complete before the candidate becomes visible
         wait_vm();
-        const bool acc = c.has && !sm.clk[l];
+        const bool acc = c.has && !locked;
         const unsigned long long dbits = acc ? delta_bits<R>(c.zn - c.zc) : 0ull;
         const unsigned long long rt = (unsigned long long)(unsigned)r << 32;
         const int w = k.w;
