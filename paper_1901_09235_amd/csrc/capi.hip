@@ -874,15 +874,23 @@ int corr64x(DeviceState *ds, hipStream_t stream, const Geom &g, const double *R6
   return corr64<Rz, MODE>(stream, g, R64, D64, pk64, o);
 }
 
-// FP64 residual res = X - Z*D of a position-major z, enqueued without host
-// synchronisation; acc[0] += sum |z|, acc[1] += nnz (acc must start at 0).
+// FP64 residual res = X - Z*D of a position-major z with its counts (meta),
+// enqueued without host synchronisation; sums[0] += sum res^2, sums[2] +=
+// sum |z|, sums[3] += nnz (they must start at 0).
 template <class R>
 int residual64_async(hipStream_t stream, const Geom &g, const R *X, const double *D64, const R *zpm, double *res,
-                     double *acc, const uint32_t *meta = nullptr) {
-  const long long nx = (long long)g.P * g.T1 * g.T2, HW = (long long)g.H * g.W;
-  hipLaunchKernelGGL((convert_kernel<R, double>), dim3(grid_stride_blocks(nx)), dim3(256), 0, stream, nx, X, res);
-  const unsigned nb = (unsigned)std::min<long long>((HW + 31) / 32, 16384);
-  hipLaunchKernelGGL((residual_dense<R, double>), dim3(nb), dim3(256), 0, stream, g, zpm, D64, res, acc, meta);
+                     double *sums, const uint32_t *meta) {
+  // tiles of 32 rows where they fill the CUs, of 8 on smaller images
+  const unsigned ntc = (g.T2 + 63) / 64;
+  if (g.T1 == 1)
+    hipLaunchKernelGGL((residual_gather<R, true, 8>), dim3((g.T2 + 255) / 256, (g.P + 7) / 8), dim3(256), 0, stream, g,
+                       X, zpm, meta, D64, res, sums);
+  else if ((long long)ntc * ((g.T1 + 31) / 32) * g.P >= 512)
+    hipLaunchKernelGGL((residual_gather<R, false, 8>), dim3(ntc * ((g.T1 + 31) / 32), g.P), dim3(256), 0, stream, g, X,
+                       zpm, meta, D64, res, sums);
+  else
+    hipLaunchKernelGGL((residual_gather<R, false, 2>), dim3(ntc * ((g.T1 + 7) / 8), g.P), dim3(256), 0, stream, g, X,
+                       zpm, meta, D64, res, sums);
   HIPCK(hipGetLastError());
   return DCDL_OK;
 }
@@ -893,10 +901,10 @@ int residual64_async(hipStream_t stream, const Geom &g, const R *X, const double
 // beta = G + n z there in FP64 rounded to R: the check doubles as a drift
 // correction.  `tm` times the contraction.
 template <class R>
-int check64(DeviceState *ds, hipStream_t stream, const Geom &g, const R *X, const R *D, const R *zpm, double lambda,
-            int positive, double *obj, double *kkt, long long *nnz, const R *beta_cmp = nullptr,
-            const double *nrm64 = nullptr, double *drift = nullptr, R *beta_fix = nullptr,
-            CorrTimer *tm = nullptr, double *g64 = nullptr, Fp64Ctx *ctx = nullptr, const uint32_t *meta = nullptr) {
+int check64(DeviceState *ds, hipStream_t stream, const Geom &g, const R *X, const R *D, const R *zpm,
+            const uint32_t *meta, double lambda, int positive, double *obj, double *kkt, long long *nnz,
+            const R *beta_cmp = nullptr, const double *nrm64 = nullptr, double *drift = nullptr, R *beta_fix = nullptr,
+            CorrTimer *tm = nullptr, double *g64 = nullptr, Fp64Ctx *ctx = nullptr) {
   const long long nd = (long long)g.K * g.P * g.L1 * g.L2, nx = (long long)g.P * g.T1 * g.T2;
   double *D64, *res, *scal;
   WS("D64", sizeof(double) * nd, D64);
@@ -904,9 +912,8 @@ int check64(DeviceState *ds, hipStream_t stream, const Geom &g, const R *X, cons
   WS("scal", 64, scal);
   hipLaunchKernelGGL((convert_kernel<R, double>), dim3(grid_stride_blocks(nd)), dim3(256), 0, stream, nd, D, D64);
   HIPCK(hipMemsetAsync(scal, 0, 40, stream));
-  int rc = residual64_async<R>(stream, g, X, D64, zpm, res, scal + 2, meta);
+  int rc = residual64_async<R>(stream, g, X, D64, zpm, res, scal, meta);
   if (rc) return rc;
-  hipLaunchKernelGGL(sum_squares, dim3(grid_stride_blocks(nx)), dim3(256), 0, stream, nx, res, scal);
   CorrOut o{};
   o.zpm = zpm;
   o.lambda = lambda;
@@ -939,8 +946,8 @@ int check64(DeviceState *ds, hipStream_t stream, const Geom &g, const R *X, cons
 // With fresh = false it reuses the residual and D64 left by check64.
 template <class R>
 int beta_from_z64(DeviceState *ds, hipStream_t stream, const Geom &g, const R *X, const R *D, const R *zpm,
-                  const double *nrm64, R *beta, bool fresh, CorrTimer *tm = nullptr, double *g64 = nullptr,
-                  Fp64Ctx *ctx = nullptr, const uint32_t *meta = nullptr) {
+                  const uint32_t *meta, const double *nrm64, R *beta, bool fresh, CorrTimer *tm = nullptr,
+                  double *g64 = nullptr, Fp64Ctx *ctx = nullptr) {
   const long long nd = (long long)g.K * g.P * g.L1 * g.L2, nx = (long long)g.P * g.T1 * g.T2;
   double *D64, *res, *scal;
   WS("D64", sizeof(double) * nd, D64);
@@ -949,7 +956,7 @@ int beta_from_z64(DeviceState *ds, hipStream_t stream, const Geom &g, const R *X
     WS("scal", 64, scal);
     hipLaunchKernelGGL((convert_kernel<R, double>), dim3(grid_stride_blocks(nd)), dim3(256), 0, stream, nd, D, D64);
     HIPCK(hipMemsetAsync(scal, 0, 32, stream));
-    int rc = residual64_async<R>(stream, g, X, D64, zpm, res, scal + 2, meta);
+    int rc = residual64_async<R>(stream, g, X, D64, zpm, res, scal, meta);
     if (rc) return rc;
   }
   CorrOut ob{};
@@ -1290,8 +1297,9 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
   CorrTimer tm_init(evs.e[3], evs.e[4]), tm64(evs.e[5], evs.e[6]);
   int init_prec = DCDL_CORR_F64;
   if (o->warm_start) {
-    launch_to_position_major<R, R>(stream, HW, g.K, g.KS, z_out, zpm);
-    if ((rc = beta_from_z64<R>(ds, stream, g, X, D, zpm, nrm64, beta, true, &tm64, nullptr, &f64))) return rc;
+    HIPCK(hipMemsetAsync(meta, 0, sizeof(uint32_t) * HW, stream));
+    launch_to_position_major<R, R>(stream, HW, g.K, g.KS, z_out, zpm, meta);
+    if ((rc = beta_from_z64<R>(ds, stream, g, X, D, zpm, meta, nrm64, beta, true, &tm64, nullptr, &f64))) return rc;
   } else {
     HIPCK(hipMemsetAsync(zpm, 0, sizeof(R) * nz, stream));
     if ((rc = beta_init<R>(ds, stream, g, X, D, o->beta_prec, beta, &tm_init, &init_prec, &f64))) return rc;
@@ -1449,7 +1457,7 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
       // chunk, and the sweep certificate could never be reached.)
       ++n_refresh;
       if ((rc = want_ref())) return rc;
-      if ((rc = beta_from_z64<R>(ds, stream, g, X, D, zpm, nrm64, beta, true, &tm64, gref, &f64, meta))) return rc;
+      if ((rc = beta_from_z64<R>(ds, stream, g, X, D, zpm, meta, nrm64, beta, true, &tm64, gref, &f64))) return rc;
       if (gref) {
         HIPCK(hipMemcpyAsync(zref, zpm, sizeof(R) * nz, hipMemcpyDeviceToDevice, stream));
         have_ref = true;
@@ -1476,8 +1484,8 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
     }
     if (!inc_used) {
       if ((rc = want_ref())) return rc;
-      rc = check64<R>(ds, stream, g, X, D, zpm, o->lambda, o->positive, &obj, &kkt, &nnz, beta, nrm64, &drift_now,
-                      beta, &tm64, gref, &f64, meta);
+      rc = check64<R>(ds, stream, g, X, D, zpm, meta, o->lambda, o->positive, &obj, &kkt, &nnz, beta, nrm64,
+                      &drift_now, beta, &tm64, gref, &f64);
       if (rc) return rc;
       have_ref = false;
     }
@@ -1821,20 +1829,23 @@ int dicodile_objective_kkt(const dcdl_shape *shape, dcdl_dtype dtype, const void
   if (!(lambda > 0)) return fail(DCDL_EINVAL, "lambda must be > 0");
   PROLOGUE();
   const long long HW = (long long)g.H * g.W, nz = HW * g.K;
-  const unsigned pb = blocks_for(HW, 256);
+  if (dtype != DCDL_F32 && dtype != DCDL_F64) return fail(DCDL_EINVAL, "unknown dtype %d", (int)dtype);
+  uint32_t *meta;
+  WS("meta_check", sizeof(uint32_t) * HW, meta);
+  HIPCK(hipMemsetAsync(meta, 0, sizeof(uint32_t) * HW, stream));
   if (dtype == DCDL_F32) {
     float *zpm;
     WS("zpm_check", sizeof(float) * nz, zpm);
-    launch_to_position_major<float, float>(stream, HW, g.K, g.KS, (const float *)z, zpm);
+    launch_to_position_major<float, float>(stream, HW, g.K, g.KS, (const float *)z, zpm, meta);
     Fp64Ctx ctx;
-    return check64<float>(ds, stream, g, (const float *)X, (const float *)D, zpm, lambda, positive, objective, kkt,
+    return check64<float>(ds, stream, g, (const float *)X, (const float *)D, zpm, meta, lambda, positive, objective, kkt,
                           nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, &ctx);
   } else if (dtype == DCDL_F64) {
     double *zpm;
     WS("zpm_check", sizeof(double) * nz, zpm);
-    launch_to_position_major<double, double>(stream, HW, g.K, g.KS, (const double *)z, zpm);
+    launch_to_position_major<double, double>(stream, HW, g.K, g.KS, (const double *)z, zpm, meta);
     Fp64Ctx ctx;
-    return check64<double>(ds, stream, g, (const double *)X, (const double *)D, zpm, lambda, positive, objective,
+    return check64<double>(ds, stream, g, (const double *)X, (const double *)D, zpm, meta, lambda, positive, objective,
                            kkt, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, &ctx);
   }
   return fail(DCDL_EINVAL, "unknown dtype %d", (int)dtype);

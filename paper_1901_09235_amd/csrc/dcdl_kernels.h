@@ -324,7 +324,7 @@ inline void launch_init_moves(hipStream_t st, long long HW, int K, int KS, const
 // copy coalesced.
 template <class Rs, class Rd>
 __global__ __launch_bounds__(256) void to_position_major(int HW, int K, int KS, const Rs *__restrict__ src,
-                                                         Rd *__restrict__ dst) {
+                                                         Rd *__restrict__ dst, uint32_t *__restrict__ meta) {
   __shared__ Rd tile[64][65];
   const long long p0 = (long long)blockIdx.x * 64;
   const int k0 = blockIdx.y * 64;
@@ -344,6 +344,12 @@ __global__ __launch_bounds__(256) void to_position_major(int HW, int K, int KS, 
   for (int i = threadIdx.x; i < pn * kn; i += 256) {
     const int pp = i / kn, kk = i - pp * kn;
     dst[(p0 + pp) * KS + k0 + kk] = tile[kk][pp];
+  }
+  // the non-zeros of each position, added to the (cleared) counts
+  if (meta && threadIdx.x < pn) {
+    int n = 0;
+    for (int kk = 0; kk < kn; ++kk) n += tile[kk][threadIdx.x] != Rd(0);
+    if (n) atomicAdd(meta + p0 + threadIdx.x, meta_pack(n));
   }
 }
 
@@ -373,9 +379,10 @@ __global__ __launch_bounds__(256) void to_atom_major(int HW, int K, int KS, cons
 }
 
 template <class Rs, class Rd>
-inline void launch_to_position_major(hipStream_t st, long long HW, int K, int KS, const Rs *src, Rd *dst) {
+inline void launch_to_position_major(hipStream_t st, long long HW, int K, int KS, const Rs *src, Rd *dst,
+                                     uint32_t *meta = nullptr) {
   hipLaunchKernelGGL((to_position_major<Rs, Rd>), dim3((unsigned)((HW + 63) / 64), (unsigned)((KS + 63) / 64)),
-                     dim3(256), 0, st, (int)HW, K, KS, src, dst);
+                     dim3(256), 0, st, (int)HW, K, KS, src, dst, meta);
 }
 
 template <class Rs, class Rd>
@@ -421,82 +428,162 @@ __global__ __launch_bounds__(256) void sum_squares(long long n, const double *__
   if (threadIdx.x == 0) atomic_add_f64(out, a);
 }
 
-// res -= Z*D for a position-major z (atom stride KS), one wave per position:
-// the lanes find the non-zero atoms of the position, then scatter each one's
-// shifted atom (eq. model) with FP64 atomics.  A wave loads the atom rows of
-// RP positions at once (RP independent loads in flight) before it scans them.
-// With `meta` (one word per position, the high 16 bits counting the non-zeros
-// of z there) a wave instead reads the words of 64 positions in one load and
-// visits only the positions whose count is not 0: z itself is read where it
-// has non-zeros.  Also accumulates sum |z| and the non-zero count into acc[0],
-// acc[1] (doubles).  No host round trip.
-template <class R, class Rd>
-__device__ __forceinline__ void residual_patch(const Geom &g, long long pos, int kb, R v, const Rd *__restrict__ D,
-                                                 double *__restrict__ res, double &l1, double &cnt) {
-  const int lane = threadIdx.x & 63;
-  unsigned long long m = __ballot(v != R(0));
-  if (!m) return;
-  if (v != R(0)) {
-    l1 += fabs((double)v);
-    cnt += 1.0;
-  }
-  const int PL = g.P * g.L1 * g.L2, LL = g.L1 * g.L2;
-  const long long plane = (long long)g.T1 * g.T2;
-  const int h = (int)(pos / g.W), w = (int)(pos - (pos / g.W) * g.W);
-  while (m) {
-    const int src = __ffsll((long long)m) - 1;
-    m &= m - 1;
-    const double zv = (double)__shfl(v, src, 64);
-    const Rd *dk = D + (long long)(kb + src) * PL;
-    for (int i = lane; i < PL; i += 64) {
-      const int p = i / LL, r = i - p * LL;
-      const int t1 = r / g.L2, t2 = r - (r / g.L2) * g.L2;
-      atomic_add_f64(res + p * plane + (long long)(h + t1) * g.T2 + (w + t2), -zv * (double)dk[i]);
-    }
-  }
-}
-
-template <class R, class Rd>
-__global__ __launch_bounds__(256) void residual_dense(Geom g, const R *__restrict__ z, const Rd *__restrict__ D,
-                                                      double *__restrict__ res, double *__restrict__ acc,
-                                                      const uint32_t *__restrict__ meta) {
-  constexpr int RP = 8;
+// res = X - Z*D in FP64 (eq. model) of a position-major z (atom stride KS) and
+// its counts (`meta`: the high 16 bits of a position's word count its
+// non-zeros), with sums[0] += sum res^2, sums[2] += sum |z| and sums[3] += the
+// number of non-zeros.  One workgroup gathers a tile of outputs: 4 NA rows x 64
+// columns of one channel, or (SIG) 256 samples of NA channels of a signal.
+//
+// It lists the non-zeros whose atoms reach the tile in LDS, as many positions
+// at a time as fit, from the counts (z is read only where they are not 0), and
+// each thread adds their atoms to its NA outputs: in registers, rows of an
+// atom read in contiguous runs, a row of the tile that an atom misses skipped
+// by the whole wave.  Scattering every atom with FP64 atomics, with the
+// conversion of X before it and the sum of squares after, was bound by the
+// atomics: 16 per nanosecond (1024^2 image, 16x16 atoms, 248,000 non-zeros:
+// 777 us).  The sums run in the order of the positions, so results repeat.
+constexpr int kResCap = 1024;  // listed non-zeros; a position has at most K <= 1024
+template <class R, bool SIG, int NA>
+__global__ __launch_bounds__(256) void residual_gather(Geom g, const R *__restrict__ X, const R *__restrict__ z,
+                                                       const uint32_t *__restrict__ meta,
+                                                       const double *__restrict__ D, double *__restrict__ res,
+                                                       double *__restrict__ sums) {
+  constexpr int TR = SIG ? 1 : 4 * NA, TC = SIG ? 256 : 64;
+  __shared__ double lz[kResCap];
+  __shared__ int lh[kResCap], lw[kResCap], lk[kResCap];
+  __shared__ int wsum[4], tot_s;
   __shared__ double sh[4];
-  const int lane = threadIdx.x & 63;
-  const long long HW = (long long)g.H * g.W;
-  double l1 = 0.0, cnt = 0.0;
-  const long long wave = (long long)blockIdx.x * 4 + (threadIdx.x >> 6), nwaves = (long long)gridDim.x * 4;
-  if (meta) {
-    for (long long c0 = wave * 64; c0 < HW; c0 += nwaves * 64) {
-      const long long mine = c0 + lane;
-      unsigned long long pm = __ballot(mine < HW && (meta[mine] >> 16) != 0);
-      while (pm) {
-        const long long pos = c0 + (__ffsll((long long)pm) - 1);
-        pm &= pm - 1;
-        for (int kb = 0; kb < g.K; kb += 64) {
-          const int k = kb + lane;
-          const R v = k < g.K ? z[pos * g.KS + k] : R(0);
-          residual_patch<R, Rd>(g, pos, kb, v, D, res, l1, cnt);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int ntc = (g.T2 + TC - 1) / TC;  // tiles in raster order along blockIdx.x, channels along y
+  const int r0 = (int)(blockIdx.x / ntc) * TR, c0 = (int)(blockIdx.x % ntc) * TC;
+  const int p0 = blockIdx.y * (SIG ? NA : 1);
+  const int col = c0 + (SIG ? tid : lane);
+  const long long plane = (long long)g.T1 * g.T2;
+  // output i: channel p0 + i (SIG) or row r0 + wave + 4 i
+  auto there = [&](int i) { return col < g.T2 && (SIG ? p0 + i < g.P : r0 + wave + 4 * i < g.T1); };
+  auto at = [&](int i) {
+    return SIG ? (long long)(p0 + i) * plane + col
+               : (long long)p0 * plane + (long long)(r0 + wave + 4 * i) * g.T2 + col;
+  };
+  double acc[NA];
+#pragma unroll
+  for (int i = 0; i < NA; ++i) acc[i] = there(i) ? (double)X[at(i)] : 0.0;
+  // positions whose atoms reach the tile
+  const int h0 = max(0, r0 - g.L1 + 1), h1 = min(g.H, r0 + TR);
+  const int w0 = max(0, c0 - g.L2 + 1), w1 = min(g.W, c0 + TC);
+  const int ww = w1 - w0, nwin = h1 > h0 && ww > 0 ? (h1 - h0) * ww : 0;
+  const int per = 4 * g.K <= kResCap ? 4 : 1;  // positions per thread and pass
+  const bool first = p0 == 0;                  // counts each non-zero once: in the tile that holds its position
+  double l1 = 0.0, cnt = 0.0, sq = 0.0;
+  for (int base = 0; base < nwin;) {
+    int n[4], nt = 0;
+    int h[4], w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int q = base + per * tid + j;
+      n[j] = 0;
+      if (j < per && q < nwin) {
+        h[j] = h0 + q / ww;
+        w[j] = w0 + q - (h[j] - h0) * ww;
+        n[j] = min((int)(meta[(long long)h[j] * g.W + w[j]] >> 16), g.K);
+        nt += n[j];
+      }
+    }
+    // this thread's place in the list; those past its end wait for the next pass
+    int off = nt;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int o = __shfl_up(off, d, 64);
+      if (lane >= d) off += o;
+    }
+    if (lane == 63) wsum[wave] = off;
+    __syncthreads();
+    for (int q = 0; q < wave; ++q) off += wsum[q];
+    const bool fit = off <= kResCap;
+    const int nfit = __syncthreads_count(fit);
+    if (tid == nfit - 1) tot_s = off;
+    off -= nt;
+    if (fit && nt)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (!n[j]) continue;
+        const R *zr = z + ((long long)h[j] * g.W + w[j]) * g.KS;
+        const int end = off + n[j];
+        const bool home = first && h[j] >= r0 && h[j] < r0 + TR && w[j] >= c0 && w[j] < c0 + TC;
+        for (int k0 = 0; k0 < g.K && off < end; k0 += 8) {
+          R zv[8];  // eight reads in flight
+#pragma unroll
+          for (int i = 0; i < 8; ++i) zv[i] = k0 + i < g.K ? zr[k0 + i] : R(0);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            if (zv[i] == R(0) || off >= end) continue;
+            lz[off] = (double)zv[i];
+            lh[off] = h[j];
+            lw[off] = w[j];
+            lk[off] = k0 + i;
+            ++off;
+            if (home) {
+              l1 += fabs((double)zv[i]);
+              cnt += 1.0;
+            }
+          }
+        }
+        for (; off < end; ++off) {  // a count beyond the row's non-zeros lists nothing
+          lz[off] = 0.0;
+          lh[off] = h[j];
+          lw[off] = w[j];
+          lk[off] = 0;
         }
       }
-    }
-  } else {
-    for (long long pos0 = wave * RP; pos0 < HW; pos0 += nwaves * RP) {
-      for (int kb = 0; kb < g.K; kb += 64) {
-        const int k = kb + lane;
-        R v[RP];
+    __syncthreads();
+    const int tot = tot_s;
+    // EU non-zeros at a time: their atom values are read before the first is used
+    constexpr int EU = 16 / NA;
+    for (int e0 = 0; e0 < tot; e0 += EU) {
+      double dv[EU][NA], zv[EU];
 #pragma unroll
-        for (int q = 0; q < RP; ++q) v[q] = (k < g.K && pos0 + q < HW) ? z[(pos0 + q) * g.KS + k] : R(0);
+      for (int q = 0; q < EU; ++q) {
+        const int e = min(e0 + q, tot - 1);
+        zv[q] = e0 + q < tot ? lz[e] : 0.0;
+        const int k = __builtin_amdgcn_readfirstlane(lk[e]), hz = __builtin_amdgcn_readfirstlane(lh[e]);
+        const int dx = col - lw[e];
+        const bool on = dx >= 0 && dx < g.L2;
+        const double *const d = D + ((long long)k * g.P + p0) * g.L1 * g.L2 + dx;
+        const int dy0 = __builtin_amdgcn_readfirstlane(r0 + wave - hz);
 #pragma unroll
-        for (int q = 0; q < RP; ++q) residual_patch<R, Rd>(g, pos0 + q, kb, v[q], D, res, l1, cnt);
+        for (int i = 0; i < NA; ++i) {
+          dv[q][i] = 0.0;
+          if (SIG) {
+            if (on && p0 + i < g.P) dv[q][i] = d[(long long)i * g.L2];
+          } else {
+            const int dy = dy0 + 4 * i;
+            if (dy >= 0 && dy < g.L1 && on) dv[q][i] = d[(long long)dy * g.L2];
+          }
+        }
       }
+#pragma unroll
+      for (int q = 0; q < EU; ++q)
+#pragma unroll
+        for (int i = 0; i < NA; ++i) acc[i] -= zv[q] * dv[q][i];
     }
+    base += per * nfit;
+    __syncthreads();
   }
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+    if (there(i)) {
+      res[at(i)] = acc[i];
+      sq += acc[i] * acc[i];
+    }
+  sq = block_sum<256>(sq, sh);
   l1 = block_sum<256>(l1, sh);
   cnt = block_sum<256>(cnt, sh);
-  if (threadIdx.x == 0) {
-    atomic_add_f64(acc, l1);
-    atomic_add_f64(acc + 1, cnt);
+  if (tid == 0) {
+    atomic_add_f64(sums, sq);
+    if (cnt != 0.0) {
+      atomic_add_f64(sums + 2, l1);
+      atomic_add_f64(sums + 3, cnt);
+    }
   }
 }
 
