@@ -1567,6 +1567,19 @@ template <class R>
 int corr_impl(DeviceState *ds, hipStream_t stream, Geom g, const R *X, const R *D, R *out, int prec) {
   g.KS = atom_stride(g.K, (int)sizeof(R));
   const long long HW = (long long)g.H * g.W;
+  if constexpr (std::is_same<R, float>::value) {
+    // (a solve keeps the other form: its start is position-major)
+    const int p = resolve_prec(prec, true, g, true);
+    if ((p == DCDL_CORR_BF16 || p == DCDL_CORR_BF16X3) && mf_row8_ok(g, mf_of(p))) {
+      void *pk;
+      WS("corr_row8", mf_row8_pack_bytes(g, mf_of(p)), pk);
+      int rc = p == DCDL_CORR_BF16 ? mf_row8_launch<1>(stream, g, X, D, pk, out)
+                                   : mf_row8_launch<2>(stream, g, X, D, pk, out);
+      if (rc) return rc;
+      HIPCK(hipStreamSynchronize(stream));
+      return DCDL_OK;
+    }
+  }
   R *gpm;
   WS("corr_pm", sizeof(R) * HW * g.KS, gpm);
   int rc = beta_init<R>(ds, stream, g, X, D, prec, gpm);

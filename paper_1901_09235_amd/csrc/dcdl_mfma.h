@@ -368,4 +368,126 @@ __global__ __launch_bounds__(256) void corr_mfma(Geom g, MfPlan pl, const Rin *_
   }
 }
 
+// ---------------------------------------- one-channel images, atom-major output
+//
+// With one channel a lane's fragment of eight reduction indices is eight
+// neighbouring pixels at any column: the layout above reads it in 2-byte
+// pieces (16 LDS reads of a split-BF16 fragment), and one step per tap row
+// leaves half of the instruction idle for atoms of 16 columns.  Here the
+// window holds, for every pixel, the 16-byte vector of the eight pixels that
+// start there, so a fragment is one aligned LDS read, and the steps run
+// through the groups of eight taps of all tap rows in turn (G8 = ceil(L2 / 8)
+// groups per row, four per step), so only the last step is padded.  G is
+// written atom-major as the caller takes it.
+//
+// 1024^2 image, 25 atoms of 16x16, split BF16: see mf_row8_launch.
+
+// Packed atoms: step s, atom tile m, lane l: the taps (t1, 8 g + e) of atom
+// 16 m + l % 16 for group q = 4 s + l / 16 = t1 G8 + g; copy 1 the low halves.
+template <int NCOPY>
+__global__ __launch_bounds__(256) void mf_row8_pack(Geom g, int G8, int MTT, const float *__restrict__ D,
+                                                    __bf16 *__restrict__ out, long long n) {
+  for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
+    const int e = (int)(i & 7), lane = (int)((i >> 3) & 63);
+    const long long r = i >> 9;
+    const int m = (int)(r % MTT), q = 4 * (int)(r / MTT) + lane / 16;
+    const int t1 = q / G8, t2 = 8 * (q - t1 * G8) + e, k = 16 * m + lane % 16;
+    const float v = k < g.K && t1 < g.L1 && t2 < g.L2 ? D[((long long)k * g.L1 + t1) * g.L2 + t2] : 0.f;
+    const __bf16 hi = (__bf16)v;
+    out[i] = hi;
+    if constexpr (NCOPY == 2) out[n + i] = (__bf16)(v - (float)hi);
+  }
+}
+
+// 4 rows x 64 columns of positions per workgroup, one row per wave, MT atom
+// tiles from m0.  LDS: NCOPY (L1 + 3) (64 + 8 G8) vectors.
+template <int NCOPY, int MT>
+__global__ __launch_bounds__(256) void corr_mfma_row8(Geom g, int G8, int MTT, const float *__restrict__ X,
+                                                      const __bf16 *__restrict__ Dpk, long long npk, int m0,
+                                                      float *__restrict__ G) {
+  constexpr int TR = 4, NTW = 4, TC = 16 * NTW;
+  extern __shared__ __align__(16) unsigned char mf_smem[];
+  mf_bf8 *const xs = reinterpret_cast<mf_bf8 *>(mf_smem);
+  const int TCX = TC + 8 * G8, nrows = TR + g.L1 - 1, copy = nrows * TCX;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int h0 = blockIdx.y * TR, w0 = blockIdx.x * TC;
+  // a run of eight pixels per thread and step: 15 loads, eight vectors
+  const int nrun = TCX / 8;
+  for (int e = tid; e < nrows * nrun; e += 256) {
+    const int r = e / nrun, c = 8 * (e - r * nrun), hh = h0 + r;
+    const float *const src = X + (long long)hh * g.T2 + w0 + c;
+    __bf16 hi[15], lo[15];
+#pragma unroll
+    for (int i = 0; i < 15; ++i) {
+      const float v = hh < g.T1 && w0 + c + i < g.T2 ? src[i] : 0.f;
+      hi[i] = (__bf16)v;
+      lo[i] = (__bf16)(v - (float)hi[i]);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      mf_bf8 a, b;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        a[i] = hi[i + j];
+        b[i] = lo[i + j];
+      }
+      xs[r * TCX + c + j] = a;
+      if constexpr (NCOPY == 2) xs[copy + r * TCX + c + j] = b;
+    }
+  }
+  __syncthreads();
+  mf_f4 acc[MT][NTW];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < NTW; ++n) acc[m][n] = mf_f4{0, 0, 0, 0};
+  const int nq = g.L1 * G8, steps = (nq + 3) / 4;
+  int t1 = (lane >> 4) / G8, gq = (lane >> 4) - t1 * G8;
+  const mf_bf8 *ap = reinterpret_cast<const mf_bf8 *>(Dpk) + (long long)m0 * 64 + lane;
+  for (int s = 0; s < steps; ++s) {
+    mf_bf8 a[NCOPY][MT], b[NCOPY][NTW];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int cp = 0; cp < NCOPY; ++cp) a[cp][m] = ap[m * 64 + cp * (npk / 8)];
+    // groups past the last tap row meet zero atoms: any row of the window
+    const mf_bf8 *const xr = xs + (wave + min(t1, g.L1 - 1)) * TCX + 8 * gq + (lane & 15);
+#pragma unroll
+    for (int n = 0; n < NTW; ++n)
+#pragma unroll
+      for (int cp = 0; cp < NCOPY; ++cp) b[cp][n] = xr[16 * n + cp * copy];
+#pragma unroll
+    for (int n = 0; n < NTW; ++n)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][m], b[0][n], acc[m][n], 0, 0, 0);
+        if constexpr (NCOPY == 2) {
+          acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][m], b[1][n], acc[m][n], 0, 0, 0);
+          acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][m], b[0][n], acc[m][n], 0, 0, 0);
+        }
+      }
+    ap += (long long)MTT * 64;
+    gq += 4;
+    while (gq >= G8) {
+      gq -= G8;
+      ++t1;
+    }
+  }
+  const int hh = h0 + wave;
+  if (hh >= g.H) return;
+  const long long HW = (long long)g.H * g.W;
+#pragma unroll
+  for (int n = 0; n < NTW; ++n) {
+    const int ww = w0 + n * 16 + (lane & 15);
+    if (ww >= g.W) continue;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int k = 16 * (m0 + m) + 4 * (lane >> 4) + v;
+        if (k < g.K) G[k * HW + (long long)hh * g.W + ww] = acc[m][n][v];
+      }
+  }
+}
+
 }  // namespace dcdl
