@@ -28,29 +28,13 @@ template <> struct Vec<float> {
   static __device__ __forceinline__ float get(const float4 &v, int e) {
     return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
   }
-  static __device__ __forceinline__ float4 fma_neg(float4 b, float4 a, float d) {
-    return make_float4(b.x - a.x * d, b.y - a.y * d, b.z - a.z * d, b.w - a.w * d);
-  }
   static __device__ __forceinline__ float4 zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
-  static __device__ __forceinline__ void set(float4 &v, int e, float x) {
-    if (e == 0) v.x = x;
-    else if (e == 1) v.y = x;
-    else if (e == 2) v.z = x;
-    else v.w = x;
-  }
 };
 template <> struct Vec<double> {
   typedef double2 T;
   static constexpr int N = 2;
   static __device__ __forceinline__ double get(const double2 &v, int e) { return e == 0 ? v.x : v.y; }
-  static __device__ __forceinline__ double2 fma_neg(double2 b, double2 a, double d) {
-    return make_double2(b.x - a.x * d, b.y - a.y * d);
-  }
   static __device__ __forceinline__ double2 zero() { return make_double2(0.0, 0.0); }
-  static __device__ __forceinline__ void set(double2 &v, int e, double x) {
-    if (e == 0) v.x = x;
-    else v.y = x;
-  }
 };
 
 // Padded atom stride: K rounded up to a whole vector.
