@@ -440,10 +440,10 @@ int fft1_atoms(hipStream_t stream, const Geom &g, const Fft1Geom &o, const Fft1B
   return DCDL_OK;
 }
 
-// The contraction corr(R64, D64) of a signal with the outputs of `o` in MODE
+// The contraction corr(R, D64) of a signal with the outputs of `o` in MODE
 // (as corr_mfma writes them), the atoms' spectra being in b.dhat.
-template <class Rz, int MODE>
-int corr_fft1(hipStream_t stream, const Geom &g, const Fft1Geom &f1, const Fft1Bufs &b, const double *R64,
+template <class Rz, int MODE, class Rin>
+int corr_fft1(hipStream_t stream, const Geom &g, const Fft1Geom &f1, const Fft1Bufs &b, const Rin *R,
               const CorrOut &o) {
   const FftGeom &f = f1.f;
   const size_t lds = sizeof(double2) * (size_t)f.M2;
@@ -451,21 +451,24 @@ int corr_fft1(hipStream_t stream, const Geom &g, const Fft1Geom &f1, const Fft1B
     Geom gc = g;
     gc.W = (int)std::min<long long>(g.W - w0, (long long)b.nbc * f1.V);
     const int nb = (gc.W + f1.V - 1) / f1.V;
-    hipLaunchKernelGGL(fft_rows_r2c<double>, dim3(nb, g.P), dim3(f1.nt), lds, stream, f, R64 + w0, (long long)g.T2,
+    hipLaunchKernelGGL(fft_rows_r2c<Rin>, dim3(nb, g.P), dim3(f1.nt), lds, stream, f, R + w0, (long long)g.T2,
                        f1.V, f.N2, (long long)g.T2 - w0, b.tw, b.xhat, (long long)nb * f.F2p);
     hipLaunchKernelGGL(fft_spec_gemm, dim3((f.F2p + 63) / 64, (nb + kSpecB - 1) / kSpecB, (g.K + 4 * kSpecK - 1) / (4 * kSpecK)),
                        dim3(256), 0, stream, g.K, g.P, nb, f.F2p, b.xhat, b.dhat, b.shat);
-    hipLaunchKernelGGL(fft_rows_c2r, dim3(nb, g.K), dim3(f1.nt), lds, stream, f, b.shat, (long long)nb * f.F2p, b.tw,
-                       b.G, (long long)gc.W, f1.V, (long long)gc.W, 1.0 / f.M2);
-    CorrOut oc = o;
-    const long long e = w0 * g.KS;
-    if (oc.beta) oc.beta = (char *)oc.beta + sizeof(Rz) * e;
-    if (oc.zpm) oc.zpm = (const char *)oc.zpm + sizeof(Rz) * e;
-    if (oc.beta_cmp) oc.beta_cmp = (const char *)oc.beta_cmp + sizeof(Rz) * e;
-    if (oc.g64) oc.g64 += e;
-    if (oc.meta) oc.meta += w0;
-    hipLaunchKernelGGL((fft_epilogue<MODE, Rz>), dim3((unsigned)std::min((gc.W + 63) / 64, 4096)), dim3(256), 0, stream,
-                       gc, b.G, oc);
+    hipLaunchKernelGGL(fft_rows_c2r<MODE == CORR_ABSMAX>, dim3(nb, g.K), dim3(f1.nt), lds, stream, f, b.shat,
+                       (long long)nb * f.F2p, b.tw, b.G, (long long)gc.W, f1.V, (long long)gc.W, 1.0 / f.M2, o.positive,
+                       o.result);
+    if constexpr (MODE != CORR_ABSMAX) {
+      CorrOut oc = o;
+      const long long e = w0 * g.KS;
+      if (oc.beta) oc.beta = (char *)oc.beta + sizeof(Rz) * e;
+      if (oc.zpm) oc.zpm = (const char *)oc.zpm + sizeof(Rz) * e;
+      if (oc.beta_cmp) oc.beta_cmp = (const char *)oc.beta_cmp + sizeof(Rz) * e;
+      if (oc.g64) oc.g64 += e;
+      if (oc.meta) oc.meta += w0;
+      hipLaunchKernelGGL((fft_epilogue<MODE, Rz>), dim3((unsigned)std::min((gc.W + 63) / 64, 4096)), dim3(256), 0, stream,
+                         gc, b.G, oc);
+    }
   }
   HIPCK(hipGetLastError());
   return DCDL_OK;
@@ -640,11 +643,13 @@ int corr_fft64(DeviceState *ds, hipStream_t stream, const Geom &g, const FftGeom
                          nk, rhat, dhat, shat);
       fft_cols_inverse(stream, f, shat, nk, g.H, tw1);
     }
-    hipLaunchKernelGGL(fft_rows_c2r, dim3(g.H, nk), dim3(kRowThreads), lds_row, stream, f, shat, f.plane, tw2,
-                       G + (long long)k0 * HW, HW, g.W, kWholeRows, scale);
+    hipLaunchKernelGGL(fft_rows_c2r<MODE == CORR_ABSMAX>, dim3(g.H, nk), dim3(kRowThreads), lds_row, stream, f, shat,
+                       f.plane, tw2, G + (long long)k0 * HW, HW, g.W, kWholeRows, scale, o.positive, o.result);
   }
-  const unsigned nb = (unsigned)std::min<long long>((HW + 63) / 64, 4096);
-  hipLaunchKernelGGL((fft_epilogue<MODE, Rz>), dim3(nb), dim3(256), 0, stream, g, G, o);
+  if constexpr (MODE != CORR_ABSMAX) {
+    const unsigned nb = (unsigned)std::min<long long>((HW + 63) / 64, 4096);
+    hipLaunchKernelGGL((fft_epilogue<MODE, Rz>), dim3(nb), dim3(256), 0, stream, g, G, o);
+  }
   HIPCK(hipGetLastError());
   return DCDL_OK;
 }
@@ -849,6 +854,21 @@ int corr64(hipStream_t stream, const Geom &g, const double *R64, const double *D
   return run_corr<double, double, Rz, MODE>(stream, g, R64, D64, o);
 }
 
+// The FP64 contraction of a signal by FFT if ctx's method picks it and memory
+// fits its workspace (*done).
+template <class Rz, int MODE, class Rin>
+int corr_fft1_if(DeviceState *ds, hipStream_t stream, const Geom &g, const Rin *R, const double *D64, const CorrOut &o,
+                 Fp64Ctx *ctx, bool *done) {
+  *done = false;
+  Fft1Geom f1;
+  if (!ctx || ds->arena || !fft1_pick(g, ctx->method, mfma64_signal_seconds(g), &f1)) return DCDL_OK;
+  Fft1Bufs b;
+  const int rc = fft1_prepare(ds, stream, g, f1, D64, ctx, &b, done);
+  if (rc || !*done) return rc;
+  ++ctx->n_fft;
+  return corr_fft1<Rz, MODE>(stream, g, f1, b, R, o);
+}
+
 // The FP64 contraction of one call: by FFT when ctx's method picks it for
 // this geometry, else corr64.
 template <class Rz, int MODE>
@@ -860,17 +880,9 @@ int corr64x(DeviceState *ds, hipStream_t stream, const Geom &g, const double *R6
     ++ctx->n_fft;
     return corr_fft64<Rz, MODE>(ds, stream, g, f, kc, R64, D64, o, ctx);
   }
-  Fft1Geom f1;
-  if (ctx && !ds->arena && fft1_pick(g, ctx->method, mfma64_signal_seconds(g), &f1)) {
-    Fft1Bufs b;
-    bool fits = false;
-    int rc = fft1_prepare(ds, stream, g, f1, D64, ctx, &b, &fits);
-    if (rc) return rc;
-    if (fits) {
-      ++ctx->n_fft;
-      return corr_fft1<Rz, MODE>(stream, g, f1, b, R64, o);
-    }
-  }
+  bool done = false;
+  const int rc = corr_fft1_if<Rz, MODE>(ds, stream, g, R64, D64, o, ctx, &done);
+  if (rc || done) return rc;
   return corr64<Rz, MODE>(stream, g, R64, D64, pk64, o);
 }
 
@@ -1596,20 +1608,24 @@ int lambda_max_impl(DeviceState *ds, hipStream_t stream, const Geom &g, const R 
                     double *out) {
   const long long nx = (long long)g.P * g.T1 * g.T2, nd = (long long)g.K * g.P * g.L1 * g.L2;
   double *X64, *D64, *scal;
-  WS("res64", sizeof(double) * nx, X64);
   WS("D64", sizeof(double) * nd, D64);
   WS("scal", 64, scal);
-  hipLaunchKernelGGL((convert_kernel<R, double>), dim3(grid_stride_blocks(nx)), dim3(256), 0, stream, nx, X, X64);
   hipLaunchKernelGGL((convert_kernel<R, double>), dim3(grid_stride_blocks(nd)), dim3(256), 0, stream, nd, D, D64);
   HIPCK(hipMemsetAsync(scal, 0, 16, stream));
   CorrOut o{};
   o.positive = positive;
   o.result = scal;
-  void *pk64;
-  int rc = pack64<double>(ds, stream, g, D64, &pk64);
-  if (rc) return rc;
   Fp64Ctx ctx;
-  if ((rc = corr64x<double, CORR_ABSMAX>(ds, stream, g, X64, D64, pk64, o, &ctx))) return rc;
+  bool done = false;
+  int rc = corr_fft1_if<double, CORR_ABSMAX>(ds, stream, g, X, D64, o, &ctx, &done);
+  if (rc) return rc;
+  if (!done) {
+    void *pk64;
+    WS("res64", sizeof(double) * nx, X64);
+    hipLaunchKernelGGL((convert_kernel<R, double>), dim3(grid_stride_blocks(nx)), dim3(256), 0, stream, nx, X, X64);
+    if ((rc = pack64<double>(ds, stream, g, D64, &pk64))) return rc;
+    if ((rc = corr64x<double, CORR_ABSMAX>(ds, stream, g, X64, D64, pk64, o, &ctx))) return rc;
+  }
   HIPCK(hipMemcpyAsync(out, scal, sizeof(double), hipMemcpyDeviceToHost, stream));
   HIPCK(hipStreamSynchronize(stream));
   return DCDL_OK;
