@@ -444,7 +444,7 @@ int fft1_atoms(hipStream_t stream, const Geom &g, const Fft1Geom &o, const Fft1B
 // (as corr_mfma writes them), the atoms' spectra being in b.dhat.
 template <class Rz, int MODE, class Rin>
 int corr_fft1(hipStream_t stream, const Geom &g, const Fft1Geom &f1, const Fft1Bufs &b, const Rin *R,
-              const CorrOut &o) {
+              const double *D64, const CorrOut &o) {
   const FftGeom &f = f1.f;
   const size_t lds = sizeof(double2) * (size_t)f.M2;
   for (long long w0 = 0; w0 < g.W; w0 += (long long)b.nbc * f1.V) {
@@ -455,9 +455,10 @@ int corr_fft1(hipStream_t stream, const Geom &g, const Fft1Geom &f1, const Fft1B
                        f1.V, f.N2, (long long)g.T2 - w0, b.tw, b.xhat, (long long)nb * f.F2p);
     hipLaunchKernelGGL(fft_spec_gemm, dim3((f.F2p + 63) / 64, (nb + kSpecB - 1) / kSpecB, (g.K + 4 * kSpecK - 1) / (4 * kSpecK)),
                        dim3(256), 0, stream, g.K, g.P, nb, f.F2p, b.xhat, b.dhat, b.shat);
-    hipLaunchKernelGGL(fft_rows_c2r<MODE == CORR_ABSMAX>, dim3(nb, g.K), dim3(f1.nt), lds, stream, f, b.shat,
+    const RowSource<Rin> src{R + w0, (long long)g.T2, D64, g.P, g.L2};
+    hipLaunchKernelGGL((fft_rows_c2r<MODE == CORR_ABSMAX, Rin>), dim3(nb, g.K), dim3(f1.nt), lds, stream, f, b.shat,
                        (long long)nb * f.F2p, b.tw, b.G, (long long)gc.W, f1.V, (long long)gc.W, 1.0 / f.M2, o.positive,
-                       o.result);
+                       o.result, src);
     if constexpr (MODE != CORR_ABSMAX) {
       CorrOut oc = o;
       const long long e = w0 * g.KS;
@@ -643,8 +644,9 @@ int corr_fft64(DeviceState *ds, hipStream_t stream, const Geom &g, const FftGeom
                          nk, rhat, dhat, shat);
       fft_cols_inverse(stream, f, shat, nk, g.H, tw1);
     }
-    hipLaunchKernelGGL(fft_rows_c2r<MODE == CORR_ABSMAX>, dim3(g.H, nk), dim3(kRowThreads), lds_row, stream, f, shat,
-                       f.plane, tw2, G + (long long)k0 * HW, HW, g.W, kWholeRows, scale, o.positive, o.result);
+    hipLaunchKernelGGL((fft_rows_c2r<MODE == CORR_ABSMAX, double>), dim3(g.H, nk), dim3(kRowThreads), lds_row, stream,
+                       f, shat, f.plane, tw2, G + (long long)k0 * HW, HW, g.W, kWholeRows, scale, o.positive, o.result,
+                       RowSource<double>{});
   }
   if constexpr (MODE != CORR_ABSMAX) {
     const unsigned nb = (unsigned)std::min<long long>((HW + 63) / 64, 4096);
@@ -730,7 +732,7 @@ int run_dtd(DeviceState *ds, hipStream_t stream, const Geom &g, const R *D, R *d
       hipLaunchKernelGGL(dtd_image<R>, dim3(grid_stride_blocks(nimg)), dim3(256), 0, stream, gi, D, img, nimg);
       CorrOut o{};
       o.beta = G;
-      if ((rc = corr_fft1<double, CORR_BETA>(stream, gi, f1, b, img, o))) return rc;
+      if ((rc = corr_fft1<double, CORR_BETA>(stream, gi, f1, b, img, D64, o))) return rc;
       const long long n = (long long)g.K * g.U2 * g.K;
       hipLaunchKernelGGL(dtd_gather<R>, dim3(grid_stride_blocks(n)), dim3(256), 0, stream, g, G, dtd, A, inv_n, n);
       HIPCK(hipGetLastError());
@@ -866,7 +868,7 @@ int corr_fft1_if(DeviceState *ds, hipStream_t stream, const Geom &g, const Rin *
   const int rc = fft1_prepare(ds, stream, g, f1, D64, ctx, &b, done);
   if (rc || !*done) return rc;
   ++ctx->n_fft;
-  return corr_fft1<Rz, MODE>(stream, g, f1, b, R, o);
+  return corr_fft1<Rz, MODE>(stream, g, f1, b, R, D64, o);
 }
 
 // The FP64 contraction of one call: by FFT when ctx's method picks it for

@@ -230,6 +230,15 @@ __global__ __launch_bounds__(kRowThreads) void fft_rows_r2c(FftGeom f, const Rin
   }
 }
 
+// What the rows of a signal's correlation are summed from: P channels of pitch
+// xp, and the K x P atoms of L taps.
+template <class Rin> struct RowSource {
+  const Rin *x;
+  long long xp;
+  const double *D;
+  int P, L;
+};
+
 // One output row h < H per workgroup (blockIdx.x), one spectrum per
 // blockIdx.y: the real row whose half spectrum is row h of S, times `scale`,
 // written for columns < W into G (row pitch W, batch stride gb, of whose
@@ -239,11 +248,15 @@ __global__ __launch_bounds__(kRowThreads) void fft_rows_r2c(FftGeom f, const Rin
 // bytes of a recording's lambda_max (32 channels of 134,001 samples, 40 atoms:
 // 209 us with it, 171 us without and with the samples read as they
 // come instead of from an FP64 copy).
-template <bool MAX>
+//
+// A sample or tap that is not finite (or overflows on the way) leaves no
+// finite value in its block, though only the outputs whose windows hold it are
+// concerned.  With src.x given, a row that comes out so is summed directly.
+template <bool MAX, class Rin>
 __global__ __launch_bounds__(kRowThreads) void fft_rows_c2r(FftGeom f, const double2 *__restrict__ S, long long sb,
                                                     const double2 *__restrict__ tw2, double *__restrict__ G,
                                                     long long gb, int W, long long total, double scale,
-                                                    int positive, double *__restrict__ result) {
+                                                    int positive, double *__restrict__ result, RowSource<Rin> src) {
   extern __shared__ double2 fsm[];
   double2 *a = fsm;
   const double2 *X = S + blockIdx.y * sb + (long long)blockIdx.x * f.F2p;
@@ -265,8 +278,21 @@ __global__ __launch_bounds__(kRowThreads) void fft_rows_c2r(FftGeom f, const dou
   }
   __syncthreads();
   lds_fft(a, f.M2, tw2, 2, true);
-  const double2 *z = a;
+  double2 *z = a;
   const int Wv = (int)min((long long)W, total - (long long)blockIdx.x * W);
+  if (src.x && !(isfinite(z[0].x) && isfinite(z[0].y))) {
+    const Rin *const x = src.x + (long long)blockIdx.x * W;
+    const double *const d = src.D + (long long)blockIdx.y * src.P * src.L;
+    __syncthreads();
+    for (int n = threadIdx.x; n < Wv; n += blockDim.x) {
+      double v = 0.0;
+      for (int p = 0; p < src.P; ++p)
+        for (int t = 0; t < src.L; ++t) v += (double)x[p * src.xp + n + t] * d[p * src.L + t];
+      ((double *)z)[n] = v;
+    }
+    scale = 1.0;
+    __syncthreads();
+  }
   if constexpr (MAX) {
     double m = 0.0;
     for (int n = threadIdx.x; n < f.M2; n += blockDim.x) {
