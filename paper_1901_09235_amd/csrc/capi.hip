@@ -692,7 +692,8 @@ int run_dtd_mfma(hipStream_t stream, const Geom &g, const Geom &gi, const R *D, 
   double *img = (double *)ws, *G = (double *)((char *)ws + w.img + w.pk);
   void *pk = (char *)ws + w.img;
   const long long nimg = (long long)gi.P * gi.T1 * gi.T2;
-  hipLaunchKernelGGL(dtd_image<R>, dim3(grid_stride_blocks(nimg)), dim3(256), 0, stream, gi, D, img, nimg);
+  hipLaunchKernelGGL(dtd_image<R>, dim3(grid_stride_blocks(nimg)), dim3(256), 0, stream, gi, D, img, nimg,
+                     (const int *)nullptr);
   const MfPlan pl = mf_plan(gi, MF_F64);
   int rc = mf_pack<R>(stream, gi, pl, MF_F64, D, pk);
   if (rc) return rc;
@@ -700,7 +701,8 @@ int run_dtd_mfma(hipStream_t stream, const Geom &g, const Geom &gi, const R *D, 
   o.beta = G;
   if ((rc = run_corr_mfma<MF_F64, CORR_BETA, double, double>(stream, gi, pl, img, pk, o))) return rc;
   const long long n = (long long)g.K * g.U1 * g.U2 * g.K;
-  hipLaunchKernelGGL(dtd_gather<R>, dim3(grid_stride_blocks(n)), dim3(256), 0, stream, g, G, dtd, A, inv_n, n);
+  hipLaunchKernelGGL(dtd_gather<R>, dim3(grid_stride_blocks(n)), dim3(256), 0, stream, g, G, dtd, A, inv_n, n,
+                     (const int *)nullptr);
   HIPCK(hipGetLastError());
   return DCDL_OK;
 }
@@ -719,8 +721,10 @@ int run_dtd(DeviceState *ds, hipStream_t stream, const Geom &g, const R *D, R *d
   if (ctx && mfma && !ds->arena && fft1_pick(gi, ctx->method, mfma64_signal_seconds(gi), &f1)) {
     const long long nd = (long long)g.K * g.P * g.L2, nimg = (long long)gi.P * gi.T2;
     double *D64;
+    int *ex;
     WS("D64", sizeof(double) * nd, D64);
-    hipLaunchKernelGGL((convert_kernel<R, double>), dim3(grid_stride_blocks(nd)), dim3(256), 0, stream, nd, D, D64);
+    WS("dtd_ex", sizeof(int) * g.K, ex);
+    hipLaunchKernelGGL(atoms64<R>, dim3(g.K), dim3(1024), 0, stream, g.P * g.L2, D, D64, ex);
     Fft1Bufs b;
     bool fits = false;
     int rc = fft1_prepare(ds, stream, gi, f1, D64, ctx, &b, &fits);
@@ -729,12 +733,12 @@ int run_dtd(DeviceState *ds, hipStream_t stream, const Geom &g, const R *D, R *d
       WS("dtd_ws", dtd_ws_bytes(gi).total(), ws);
       const DtdWs w = dtd_ws_bytes(gi);
       double *img = (double *)ws, *G = (double *)((char *)ws + w.img + w.pk);
-      hipLaunchKernelGGL(dtd_image<R>, dim3(grid_stride_blocks(nimg)), dim3(256), 0, stream, gi, D, img, nimg);
+      hipLaunchKernelGGL(dtd_image<R>, dim3(grid_stride_blocks(nimg)), dim3(256), 0, stream, gi, D, img, nimg, ex);
       CorrOut o{};
       o.beta = G;
       if ((rc = corr_fft1<double, CORR_BETA>(stream, gi, f1, b, img, D64, o))) return rc;
       const long long n = (long long)g.K * g.U2 * g.K;
-      hipLaunchKernelGGL(dtd_gather<R>, dim3(grid_stride_blocks(n)), dim3(256), 0, stream, g, G, dtd, A, inv_n, n);
+      hipLaunchKernelGGL(dtd_gather<R>, dim3(grid_stride_blocks(n)), dim3(256), 0, stream, g, G, dtd, A, inv_n, n, ex);
       HIPCK(hipGetLastError());
       return DCDL_OK;
     }

@@ -86,17 +86,46 @@ __global__ __launch_bounds__(256) void dtd_kernel(Geom g, const R *__restrict__ 
   }
 }
 
-// ------------------------------------------------ DtD on the matrix cores
+// D in FP64, and of every atom the exponent of its norm, about log2 ||D_k||
+// (kZeroAtom: all taps are 0).  One workgroup per atom of PL taps.  A transform
+// rounds in proportion to the largest atom of its block: scaled to norms of
+// about 1, every entry of DtD is as exact beside ||D_k|| ||D_k0|| as by direct
+// sums, whatever the atoms next to it in the DtD image.
+constexpr int kZeroAtom = -(1 << 30);
+template <class R>
+__global__ __launch_bounds__(1024) void atoms64(int PL, const R *__restrict__ D, double *__restrict__ D64,
+                                               int *__restrict__ ex) {
+  __shared__ double sh[16];
+  const long long at = (long long)blockIdx.x * PL;
+  double sq = 0.0, mx = 0.0;
+  for (int i = threadIdx.x; i < PL; i += 1024) {
+    const double v = (double)D[at + i];
+    D64[at + i] = v;
+    sq += v * v;
+    mx = fmax(mx, fabs(v));
+    if (v != v) mx = fmax(mx, 1.0);  // not a zero atom
+  }
+  sq = block_sum<1024>(sq, sh);
+  mx = block_max<1024>(mx, sh);
+  if (threadIdx.x) return;
+  if (sq > 1e-250 && sq < 1e250)
+    ex[blockIdx.x] = ilogb(sq) / 2;
+  else
+    ex[blockIdx.x] = mx == 0.0 ? kZeroAtom : isfinite(mx) ? ilogb(mx) : 0;
+}
+
+// ------------------------------------------------ DtD as a correlation
 // DtD is itself a correlation with D.  Lay the atoms side by side along the
 // second axis, atom k0 at columns k0 U2 + L2 - 1 ... k0 U2 + 2 L2 - 2 and rows
 // L1 - 1 ... 2 L1 - 2, zeros elsewhere (the L - 1 zeros between neighbours
 // serve both); this image has 3 L1 - 2 rows and K U2 + L2 - 1 columns.  Its
 // valid correlation with D (U1 rows, K U2 columns) is, at row a1 and column
 // k0 U2 + a2, sum_t D_k[t] D_k0[t + (a1, a2) - (L - 1)]: the apply-table entry
-// A[k0][a1][a2][k], i.e. dtd[k0][k] at lag (L - 1) - (a1, a2).
+// A[k0][a1][a2][k], i.e. dtd[k0][k] at lag (L - 1) - (a1, a2).  With ex
+// (atoms64), atom k0 is laid down scaled by 2^-ex[k0].
 template <class R>
 __global__ __launch_bounds__(256) void dtd_image(Geom gi, const R *__restrict__ D, double *__restrict__ img,
-                                                 long long n) {
+                                                 long long n, const int *__restrict__ ex) {
   for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
     const int a2 = (int)(i % gi.T2);
     const long long q = i / gi.T2;
@@ -105,24 +134,35 @@ __global__ __launch_bounds__(256) void dtd_image(Geom gi, const R *__restrict__ 
     double v = 0.0;
     if (t1 >= 0 && t1 < gi.L1 && c >= 0) {
       const int k0 = c / gi.U2, t2 = c - k0 * gi.U2;
-      if (k0 < gi.K && t2 < gi.L2) v = (double)D[(((long long)k0 * gi.P + p) * gi.L1 + t1) * gi.L2 + t2];
+      if (k0 < gi.K && t2 < gi.L2) {
+        v = (double)D[(((long long)k0 * gi.P + p) * gi.L1 + t1) * gi.L2 + t2];
+        if (ex && v != 0.0) v = ldexp(v, -ex[k0]);
+      }
     }
     img[i] = v;
   }
 }
 
 // dtd, the apply table (atom stride g.KS, padding left as set by the caller)
-// and 1/||D_k||^2 from G = corr(dtd_image, D) stored (U1, K U2, K).
+// and 1/||D_k||^2 from G = corr(dtd_image, D) stored (U1, K U2, K), the image
+// with the same ex.
 template <class R>
 __global__ __launch_bounds__(256) void dtd_gather(Geom g, const double *__restrict__ G, R *__restrict__ dtd,
-                                                  R *__restrict__ A, R *__restrict__ inv_n, long long n) {
+                                                  R *__restrict__ A, R *__restrict__ inv_n, long long n,
+                                                  const int *__restrict__ ex) {
   for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
     const int k = (int)(i % g.K);
     long long q = i / g.K;
     const int a2 = (int)(q % g.U2);
     q /= g.U2;
     const int a1 = (int)(q % g.U1), k0 = (int)(q / g.U1);
-    const double v = G[(((long long)a1 * g.K + k0) * g.U2 + a2) * g.K + k];
+    double v = G[(((long long)a1 * g.K + k0) * g.U2 + a2) * g.K + k];
+    if (ex) {
+      if (ex[k] != kZeroAtom && ex[k0] != kZeroAtom)
+        v = ldexp(v, ex[k0]);
+      else if (isfinite(v))
+        v = 0.0;
+    }
     A[(((long long)k0 * g.U1 + a1) * g.U2 + a2) * g.KS + k] = (R)v;
     dtd[(((long long)k0 * g.K + k) * g.U1 + (g.U1 - 1 - a1)) * g.U2 + (g.U2 - 1 - a2)] = (R)v;
     if (k == k0 && a1 == g.L1 - 1 && a2 == g.L2 - 1) inv_n[k] = (R)(1.0 / v);
