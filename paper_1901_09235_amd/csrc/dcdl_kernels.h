@@ -543,6 +543,7 @@ __global__ __launch_bounds__(256) void residual_gather(Geom g, const R *__restri
     const int nfit = __syncthreads_count(fit);
     if (tid == nfit - 1) tot_s = off;
     off -= nt;
+    bool inf = false;  // a listed value is not finite
     if (fit && nt)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -562,6 +563,7 @@ __global__ __launch_bounds__(256) void residual_gather(Geom g, const R *__restri
             lw[off] = w[j];
             lk[off] = k0 + i;
             ++off;
+            inf |= !isfinite(zv[i]);
             if (home) {
               l1 += fabs((double)zv[i]);
               cnt += 1.0;
@@ -571,15 +573,25 @@ __global__ __launch_bounds__(256) void residual_gather(Geom g, const R *__restri
         for (; off < end; ++off) {  // a count beyond the row's non-zeros lists nothing
           lz[off] = 0.0;
           lh[off] = h[j];
-          lw[off] = w[j];
+          lw[off] = 0x7fffffff;
           lk[off] = 0;
         }
       }
-    __syncthreads();
+    const bool any_inf = __syncthreads_or(inf);
     const int tot = tot_s;
+    if (any_inf)  // outputs that an atom misses must not meet its value: 0 times infinity
+      for (int e = 0; e < tot; ++e) {
+        const int dx = col - lw[e];
+        const double *const d = D + ((long long)lk[e] * g.P + p0) * g.L1 * g.L2 + dx;
+        for (int i = 0; i < NA; ++i) {
+          const int dy = SIG ? 0 : r0 + wave + 4 * i - lh[e];
+          if (dx >= 0 && dx < g.L2 && dy >= 0 && dy < g.L1 && (!SIG || p0 + i < g.P))
+            acc[i] -= lz[e] * d[(long long)(SIG ? i : dy) * g.L2];
+        }
+      }
     // EU non-zeros at a time: their atom values are read before the first is used
     constexpr int EU = 16 / NA;
-    for (int e0 = 0; e0 < tot; e0 += EU) {
+    for (int e0 = 0; e0 < (any_inf ? 0 : tot); e0 += EU) {
       double dv[EU][NA], zv[EU];
 #pragma unroll
       for (int q = 0; q < EU; ++q) {
@@ -587,7 +599,7 @@ __global__ __launch_bounds__(256) void residual_gather(Geom g, const R *__restri
         zv[q] = e0 + q < tot ? lz[e] : 0.0;
         const int k = __builtin_amdgcn_readfirstlane(lk[e]), hz = __builtin_amdgcn_readfirstlane(lh[e]);
         const int dx = col - lw[e];
-        const bool on = dx >= 0 && dx < g.L2;
+        const bool on = dx >= 0 && dx < g.L2 && e0 + q < tot;
         const double *const d = D + ((long long)k * g.P + p0) * g.L1 * g.L2 + dx;
         const int dy0 = __builtin_amdgcn_readfirstlane(r0 + wave - hz);
 #pragma unroll
