@@ -892,23 +892,83 @@ int corr64x(DeviceState *ds, hipStream_t stream, const Geom &g, const double *R6
   return corr64<Rz, MODE>(stream, g, R64, D64, pk64, o);
 }
 
+// How the residual of g is formed: gathered per tile with `na` outputs per
+// thread (residual_gather), or scattered.
+struct ResPlan {
+  bool scatter;
+  int na;
+};
+
+// Gather tiles are the largest of up to about 1.5 atom heights (every tile adds
+// the atoms that reach it from outside) and of the channels of a signal that
+// leave 448 workgroups.  Listing and adding a non-zero takes a workgroup 60 to
+// 250 ns of a busy CU and no less than 170 ns: small images and long atoms,
+// where few workgroups each add nearly every non-zero, and small atoms, which
+// fill little of a tile, are slower gathered.  A scattered non-zero costs the
+// issue of its atomics (120 values per ns), and the scatter two more passes over
+// the residual.  Compared at 0.15 non-zeros per position.  Objective calls, us,
+// gathered / scattered and which the rule takes: 1024^2 image and 16x16 atoms,
+// 1.25 non-zeros per position 2283 / 3053 g, 0.025: 469 / 591 g; 3x3 atoms,
+// 1.25: 785 / 527 s; 64^2 and 32x32 atoms, 1.25: 405 / 231 s, 0.05: 191 / 190 s;
+// 128^2 and 12x12 atoms, 0.03: 78 / 91 s; 32 x 134,001 samples, 128 taps, 0.04:
+// 308 / 558 g.
+ResPlan plan_residual(const Geom &g) {
+  const bool sig = g.T1 == 1;
+  auto wgs = [&](int na) -> double {
+    return sig ? (double)((g.T2 + 255) / 256) * ((g.P + na - 1) / na)
+               : (double)((g.T2 + 63) / 64) * ((g.T1 + 4 * na - 1) / (4 * na)) * g.P;
+  };
+  int na = 8;
+  while (na > 1 && (wgs(na) < 448 || (sig ? na > g.P : 4 * na > std::max(8, 3 * g.L1 / 2)))) na /= 2;
+  const double busy_ns = na == 1 ? 60 : na == 2 ? 100 : na == 4 ? 160 : 250;
+  // positions whose atoms reach a tile, on average
+  auto reach = [](int N, int L, int TL, int T) {
+    return std::min<double>(N, N * (1.0 + (L - 1.0) / TL) / ((T + TL - 1) / TL));
+  };
+  const int TR = sig ? 1 : 4 * na, TC = sig ? 256 : 64;
+  const double gather_ns = reach(g.H, g.L1, TR, g.T1) * reach(g.W, g.L2, TC, g.T2) * std::max(170.0, wgs(na) / 256 * busy_ns);
+  const double scatter_ns = (double)g.H * g.W * (0.12 + (double)g.P * g.L1 * g.L2 / 120);
+  const double passes_ns = 10e3 + 5e-3 * g.P * (double)g.T1 * g.T2;
+  return ResPlan{0.15 * gather_ns > 0.15 * scatter_ns + passes_ns, na};
+}
+
+template <class R, bool SIG, int NA>
+void gather_residual(hipStream_t stream, const Geom &g, const R *X, const double *D64, const R *zpm, double *res,
+                     double *sums, const uint32_t *meta) {
+  const dim3 grid = SIG ? dim3((g.T2 + 255) / 256, (g.P + NA - 1) / NA)
+                        : dim3((unsigned)((g.T2 + 63) / 64) * ((g.T1 + 4 * NA - 1) / (4 * NA)), g.P);
+  hipLaunchKernelGGL((residual_gather<R, SIG, NA>), grid, dim3(256), 0, stream, g, X, zpm, meta, D64, res, sums);
+}
+
 // FP64 residual res = X - Z*D of a position-major z with its counts (meta),
 // enqueued without host synchronisation; sums[0] += sum res^2, sums[2] +=
 // sum |z|, sums[3] += nnz (they must start at 0).
 template <class R>
 int residual64_async(hipStream_t stream, const Geom &g, const R *X, const double *D64, const R *zpm, double *res,
                      double *sums, const uint32_t *meta) {
-  // tiles of 32 rows where they fill the CUs, of 8 on smaller images
-  const unsigned ntc = (g.T2 + 63) / 64;
-  if (g.T1 == 1)
-    hipLaunchKernelGGL((residual_gather<R, true, 8>), dim3((g.T2 + 255) / 256, (g.P + 7) / 8), dim3(256), 0, stream, g,
-                       X, zpm, meta, D64, res, sums);
-  else if ((long long)ntc * ((g.T1 + 31) / 32) * g.P >= 512)
-    hipLaunchKernelGGL((residual_gather<R, false, 8>), dim3(ntc * ((g.T1 + 31) / 32), g.P), dim3(256), 0, stream, g, X,
-                       zpm, meta, D64, res, sums);
-  else
-    hipLaunchKernelGGL((residual_gather<R, false, 2>), dim3(ntc * ((g.T1 + 7) / 8), g.P), dim3(256), 0, stream, g, X,
-                       zpm, meta, D64, res, sums);
+  const ResPlan pl = plan_residual(g);
+  if (pl.scatter) {
+    const long long nx = (long long)g.P * g.T1 * g.T2, HW = (long long)g.H * g.W;
+    const int chunk = (int)std::max(1ll, std::min(64ll, HW / 1024));  // about 256 workgroups on small images
+    hipLaunchKernelGGL((convert_kernel<R, double>), dim3(grid_stride_blocks(nx)), dim3(256), 0, stream, nx, X, res);
+    hipLaunchKernelGGL(residual_scatter<R>, dim3((unsigned)std::min<long long>((HW + 4 * chunk - 1) / (4 * chunk), 4096)),
+                       dim3(256), 0, stream, g, chunk, zpm, meta, D64, res, sums);
+    hipLaunchKernelGGL(sum_squares, dim3(grid_stride_blocks(nx)), dim3(256), 0, stream, nx, res, sums);
+  } else if (g.T1 == 1) {
+    switch (pl.na) {
+      case 1: gather_residual<R, true, 1>(stream, g, X, D64, zpm, res, sums, meta); break;
+      case 2: gather_residual<R, true, 2>(stream, g, X, D64, zpm, res, sums, meta); break;
+      case 4: gather_residual<R, true, 4>(stream, g, X, D64, zpm, res, sums, meta); break;
+      default: gather_residual<R, true, 8>(stream, g, X, D64, zpm, res, sums, meta);
+    }
+  } else {
+    switch (pl.na) {
+      case 1: gather_residual<R, false, 1>(stream, g, X, D64, zpm, res, sums, meta); break;
+      case 2: gather_residual<R, false, 2>(stream, g, X, D64, zpm, res, sums, meta); break;
+      case 4: gather_residual<R, false, 4>(stream, g, X, D64, zpm, res, sums, meta); break;
+      default: gather_residual<R, false, 8>(stream, g, X, D64, zpm, res, sums, meta);
+    }
+  }
   HIPCK(hipGetLastError());
   return DCDL_OK;
 }
@@ -1315,7 +1375,7 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
   CorrTimer tm_init(evs.e[3], evs.e[4]), tm64(evs.e[5], evs.e[6]);
   int init_prec = DCDL_CORR_F64;
   if (o->warm_start) {
-    HIPCK(hipMemsetAsync(meta, 0, sizeof(uint32_t) * HW, stream));
+    if (g.KS > 64) HIPCK(hipMemsetAsync(meta, 0, sizeof(uint32_t) * HW, stream));
     launch_to_position_major<R, R>(stream, HW, g.K, g.KS, z_out, zpm, meta);
     if ((rc = beta_from_z64<R>(ds, stream, g, X, D, zpm, meta, nrm64, beta, true, &tm64, nullptr, &f64))) return rc;
   } else {
@@ -1867,7 +1927,7 @@ int dicodile_objective_kkt(const dcdl_shape *shape, dcdl_dtype dtype, const void
   if (dtype != DCDL_F32 && dtype != DCDL_F64) return fail(DCDL_EINVAL, "unknown dtype %d", (int)dtype);
   uint32_t *meta;
   WS("meta_check", sizeof(uint32_t) * HW, meta);
-  HIPCK(hipMemsetAsync(meta, 0, sizeof(uint32_t) * HW, stream));
+  if (g.KS > 64) HIPCK(hipMemsetAsync(meta, 0, sizeof(uint32_t) * HW, stream));
   if (dtype == DCDL_F32) {
     float *zpm;
     WS("zpm_check", sizeof(float) * nz, zpm);

@@ -361,7 +361,8 @@ inline void launch_init_moves(hipStream_t st, long long HW, int K, int KS, const
 // ---------------------------------------------------------------- layouts
 // user (K, H*W) <-> position-major (H*W, KS) with zero padding, and a type
 // change: LDS-tiled transposes of 64 positions x 64 atoms, both sides of the
-// copy coalesced.
+// copy coalesced.  meta, if given, receives the count of a position's non-zeros
+// (more than 64 atoms: added to it, cleared by the caller).
 template <class Rs, class Rd>
 __global__ __launch_bounds__(256) void to_position_major(int HW, int K, int KS, const Rs *__restrict__ src,
                                                          Rd *__restrict__ dst, uint32_t *__restrict__ meta) {
@@ -385,11 +386,15 @@ __global__ __launch_bounds__(256) void to_position_major(int HW, int K, int KS, 
     const int pp = i / kn, kk = i - pp * kn;
     dst[(p0 + pp) * KS + k0 + kk] = tile[kk][pp];
   }
-  // the non-zeros of each position, added to the (cleared) counts
+  // the non-zeros of each position, added to the cleared counts where several
+  // workgroups hold a position's atoms
   if (meta && threadIdx.x < pn) {
     int n = 0;
     for (int kk = 0; kk < kn; ++kk) n += tile[kk][threadIdx.x] != Rd(0);
-    if (n) atomicAdd(meta + p0 + threadIdx.x, meta_pack(n));
+    if (gridDim.y == 1)
+      meta[p0 + threadIdx.x] = meta_pack(n);
+    else if (n)
+      atomicAdd(meta + p0 + threadIdx.x, meta_pack(n));
   }
 }
 
@@ -478,10 +483,11 @@ __global__ __launch_bounds__(256) void sum_squares(long long n, const double *__
 // at a time as fit, from the counts (z is read only where they are not 0), and
 // each thread adds their atoms to its NA outputs: in registers, rows of an
 // atom read in contiguous runs, a row of the tile that an atom misses skipped
-// by the whole wave.  Scattering every atom with FP64 atomics, with the
-// conversion of X before it and the sum of squares after, was bound by the
-// atomics: 16 per nanosecond (1024^2 image, 16x16 atoms, 248,000 non-zeros:
-// 777 us).  The sums run in the order of the positions, so results repeat.
+// by the whole wave.  The scatter (residual_scatter) converts X, adds every atom
+// with FP64 atomics, 80 to 120 values per ns, and sums the squares in a pass of
+// its own (1024^2 image, 16x16 atoms, 248,000 non-zeros: 777 us).  The outputs
+// are summed in the order of the positions, so the residual repeats bit for
+// bit; the three sums over workgroups do not.
 constexpr int kResCap = 1024;  // listed non-zeros; a position has at most K <= 1024
 template <class R, bool SIG, int NA>
 __global__ __launch_bounds__(256) void residual_gather(Geom g, const R *__restrict__ X, const R *__restrict__ z,
@@ -636,6 +642,56 @@ __global__ __launch_bounds__(256) void residual_gather(Geom g, const R *__restri
       atomic_add_f64(sums + 2, l1);
       atomic_add_f64(sums + 3, cnt);
     }
+  }
+}
+
+// The same residual by scatter: res = X on entry; a wave takes the positions
+// with non-zeros among `chunk` <= 64 neighbours (their counts are one load), and
+// its lanes find a position's non-zero atoms and subtract each one's shifted
+// copy with FP64 atomics.  sums[2] += sum |z| and sums[3] += the number of
+// non-zeros.
+template <class R>
+__global__ __launch_bounds__(256) void residual_scatter(Geom g, int chunk, const R *__restrict__ z,
+                                                        const uint32_t *__restrict__ meta,
+                                                        const double *__restrict__ D, double *__restrict__ res,
+                                                        double *__restrict__ sums) {
+  __shared__ double sh[4];
+  const int lane = threadIdx.x & 63, LL = g.L1 * g.L2, PL = g.P * LL;
+  const long long HW = (long long)g.H * g.W, plane = (long long)g.T1 * g.T2;
+  double l1 = 0.0, cnt = 0.0;
+  const long long wave = (long long)blockIdx.x * 4 + (threadIdx.x >> 6), nwaves = (long long)gridDim.x * 4;
+  for (long long c0 = wave * chunk; c0 < HW; c0 += nwaves * chunk) {
+    const long long mine = c0 + lane;
+    unsigned long long pm = __ballot(lane < chunk && mine < HW && (meta[mine] >> 16) != 0);
+    while (pm) {
+      const long long pos = c0 + (__ffsll((long long)pm) - 1);
+      pm &= pm - 1;
+      const int h = (int)(pos / g.W), w = (int)(pos - (long long)h * g.W);
+      for (int kb = 0; kb < g.K; kb += 64) {
+        const R v = kb + lane < g.K ? z[pos * g.KS + kb + lane] : R(0);
+        unsigned long long m = __ballot(v != R(0));
+        if (v != R(0)) {
+          l1 += fabs((double)v);
+          cnt += 1.0;
+        }
+        while (m) {
+          const int src = __ffsll((long long)m) - 1;
+          m &= m - 1;
+          const double zv = (double)__shfl(v, src, 64);
+          const double *const dk = D + (long long)(kb + src) * PL;
+          for (int i = lane; i < PL; i += 64) {
+            const int p = i / LL, r = i - p * LL, t1 = r / g.L2, t2 = r - t1 * g.L2;
+            atomic_add_f64(res + p * plane + (long long)(h + t1) * g.T2 + (w + t2), -zv * dk[i]);
+          }
+        }
+      }
+    }
+  }
+  l1 = block_sum<256>(l1, sh);
+  cnt = block_sum<256>(cnt, sh);
+  if (threadIdx.x == 0 && cnt != 0.0) {
+    atomic_add_f64(sums + 2, l1);
+    atomic_add_f64(sums + 3, cnt);
   }
 }
 
