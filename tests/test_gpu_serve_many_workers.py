@@ -1,0 +1,57 @@
+"""Servers whose ready requests ask for more workers than one launch holds, and
+requests whose worker grids do not divide into teams: every request is solved
+as dicodile_csc solves it on its own (FP64: the same minimiser to 1e-6 of its
+largest value; objectives to 1e-9)."""
+import numpy as np
+import pytest
+
+from paper_1901_09235_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def lib():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1901_09235_amd as dl
+    dl.load()
+    return dl
+
+
+def dev(a, dtype):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(device="cuda", dtype=dtype)
+
+
+def serve(lib, pbs, D, dtype, rel, **kw):
+    """Every problem through one server at once; compared with its own solve."""
+    Dd = dev(D, dtype)
+    Xs = [dev(pb.X, dtype) for pb in pbs]
+    lams = [0.2 * lib.dicodile_lambda_max(X, Dd) for X in Xs]
+    torch.cuda.synchronize()
+    with lib.Server(Dd, **kw) as srv:
+        tickets = [srv.submit(X, lam, rel * lam, timeout_s=60) for X, lam in zip(Xs, lams)]
+        res = [srv.wait(t, timeout_s=120) for t in tickets]
+        st = srv.stats()
+    for X, lam, (z, info) in zip(Xs, lams, res):
+        assert info["status"] == "OK", info
+        z1, one = lib.dicodile_csc(X, Dd, lam, rel * lam, timeout_s=60)
+        assert info["objective"] == pytest.approx(one["objective"], rel=1e-9 if dtype == torch.float64 else 1e-6)
+        if dtype == torch.float64:
+            assert float((z - z1).abs().max()) <= 1e-6 * float(z1.abs().max())
+    return st, [info["grid"] for _, info in res]
+
+
+def test_fp64_requests_of_more_workers_than_a_launch_holds(lib):
+    """admit_workers = -1 admits all eight requests of 128 workers; a launch of
+    FP64 workers of 256 threads holds three per CU."""
+    D = synth.gaussian_dictionary(np.random.Generator(np.random.PCG64(21)), 5, 1, 64)
+    pbs = [synth.make_problem(f"r{i}", 2100 + i, P=1, T=20000 + 37 * i, K=5, L=64, rho=0.004, amp="uniform",
+                              sigma=0.1, D=D) for i in range(8)]
+    st, grids = serve(lib, pbs, D, torch.float64, 1e-9, admit_workers=-1, max_len=32768)
+    assert all(g == (1, 128) for g in grids)
+    assert st["peak_active"] == 8
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert st["peak_workers"] <= 3 * cus
