@@ -55,3 +55,21 @@ def test_fp64_requests_of_more_workers_than_a_launch_holds(lib):
     assert st["peak_active"] == 8
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     assert st["peak_workers"] <= 3 * cus
+
+
+def test_image_request_whose_workers_make_too_many_teams(lib):
+    """31 x 33 workers: 264 teams of four, more than one per CU, in one request."""
+    D = synth.gaussian_dictionary(np.random.Generator(np.random.PCG64(22)), 4, 1, (10, 10))
+    pbs = [synth.make_problem(f"i{i}", 2200 + i, P=1, T=t, K=4, L=(10, 10), rho=0.002, amp="uniform", sigma=0.1, D=D)
+           for i, t in enumerate([(324, 344), (60, 70), (324, 344)])]
+    _, grids = serve(lib, pbs, D, torch.float32, 1e-5, max_workers=1024, tile=(10, 10), max_len=1 << 17)
+    assert grids[0] == (31, 33) and grids[2] == (31, 33)
+
+
+def test_many_requests_of_a_few_workers(lib):
+    """150 requests of five workers each: 300 teams of four, 750 workgroups of one."""
+    D = synth.gaussian_dictionary(np.random.Generator(np.random.PCG64(23)), 32, 1, 64)
+    pbs = [synth.make_problem(f"r{i}", 2300 + i, P=1, T=1663 + i, K=32, L=64, rho=0.001, amp="uniform", sigma=0.1, D=D)
+           for i in range(150)]
+    _, grids = serve(lib, pbs, D, torch.float32, 1e-5, tile=320, slice_rounds=16)
+    assert all(g == (1, 5) for g in grids)
