@@ -1337,7 +1337,9 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
   std::vector<Teams> teams;
   const int wg_nt = plan_teams({{pl.W1, pl.W2}}, patch_lanes_of(g, Vec<R>::N), ds->cus, &teams);
   const int nwg = teams[0].count();
-  const bool ext = o->strategy == DCDL_SELECT_RANDOM || o->inner > 1;
+  // visits per round: at most the sub-domains of the largest worker
+  const int inner = o->strategy == DCDL_SELECT_RANDOM ? 1 : std::max(1, std::min(o->inner, pl.mmax));
+  const bool ext = o->strategy == DCDL_SELECT_RANDOM || inner > 1;
 
   R *beta, *zpm, *A, *dtd, *inv_n, *score;
   uint32_t *meta;
@@ -1405,7 +1407,7 @@ int csc_impl(DeviceState *ds, hipStream_t stream, const Geom &g_user, int ndim, 
   hi.tile1 = pl.tile1;
   hi.tile2 = pl.tile2;
   hi.mmax = pl.mmax;
-  hi.inner = o->inner > 0 ? o->inner : 1;
+  hi.inner = inner;
   hi.wg_base = 0;
   hi.positive = o->positive;
   hi.certify = o->certify;

@@ -1313,7 +1313,7 @@ __device__ __forceinline__ void run_team(CInst<R> *const I0, const int team, con
           const bool hit = __any(vs >= tol && vs > R(0));
           const long long visit = k.cursor;
           if (hit) {
-            if (inner == 1) {
+            if (inner == 1 || Mw == 1) {  // (a worker of one sub-domain makes one visit)
               c.has = true;
               c.bs = vs;
               c.bp = vp;
