@@ -1721,7 +1721,8 @@ int validate_csc(const dcdl_shape *shape, const void *X, const void *D, const dc
 
 // Scratch bytes a solve carves (every workspace slot of csc_impl and the
 // calls it makes, each rounded up to 256 bytes), with the worker count bounded
-// by 8192 workgroups.
+// by 8192 in the per-worker words and by 4096 (16 per CU of 256; a grid takes at
+// most four) in the candidate words.
 size_t csc_scratch_need(const Geom &g_user, const dcdl_csc_opts *o) {
   const bool f32 = o->dtype == DCDL_F32;
   const size_t es = f32 ? 4 : 8;
@@ -1731,7 +1732,7 @@ size_t csc_scratch_need(const Geom &g_user, const dcdl_csc_opts *o) {
   const size_t HW = (size_t)g.H * g.W, nz = HW * g.KS, nA = (size_t)g.K * g.U1 * g.U2 * g.KS;
   const size_t nW = 8192;
   size_t need = 2 * r(es * nz) + r(es * HW) + r(4 * HW) + r(es * nA) + r(es * g.K * g.K * g.U1 * g.U2) +
-                r(es * g.KS) + r(8 * (size_t)g.K) + r(8 * kCandWords * nW) + 2 * r(4 * nW) +
+                r(es * g.KS) + r(8 * (size_t)g.K) + r(8 * kCandWords * (nW / 2)) + 2 * r(4 * nW) +
                 r(sizeof(Ctl) + sizeof(int) * 2 * kRing) + r(std::max(sizeof(Inst<float>), sizeof(Inst<double>)));
   need += r(8 * (size_t)g.K * g.P * g.L1 * g.L2) + r(8 * (size_t)g.P * g.T1 * g.T2) + r(64);
   Geom gi;
