@@ -394,7 +394,7 @@ bool fft1_geom(const Geom &g, Fft1Geom *o) {
   o->f.F2p = (N2 / 2 + 1 + 15) / 16 * 16;
   o->f.plane = o->f.F2p;
   o->V = N2 - g.L2 + 1;
-  o->nt = N2 == 1024 ? 64 : kRowThreads;
+  o->nt = std::max(64, lds_fft_threads(N2 / 2));
   return true;
 }
 

@@ -139,47 +139,48 @@ __device__ __forceinline__ void stage_twiddles(double2 *w, const double2 *__rest
 // in and out) of n points in LDS buffer a, span Ns: butterfly j reads
 // a[j + r n / R], twiddles them by exp(-+2 pi i r (j mod Ns) / (Ns R)), takes
 // the R-point DFT and writes a[(j / Ns) Ns R + (j mod Ns) + r Ns].  In place:
-// every read precedes a barrier before the writes.  At most 512 butterflies,
-// one per thread of the 512-thread row workgroups.  tw[m tws] =
-// exp(-2 pi i m / n).
+// every read precedes a barrier before the writes.  Every thread of the
+// workgroup calls it, at least as many as butterflies (blockDim.x >= n / R: one
+// each, further ones idle).  tw[m tws] = exp(-2 pi i m / n).
 template <int R>
 __device__ __forceinline__ void lds_stage(double2 *a, int n, int Ns, const double2 *__restrict__ tw, int tws,
                                           bool inverse) {
-  constexpr int Q = 512 / kRowThreads;
-  const int nb = n / R;
-  double2 v[Q][R];
+  const int nb = n / R, j = threadIdx.x, jm = j & (Ns - 1);
+  double2 v[R];
+  if (j < nb) {
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const int j = threadIdx.x + q * blockDim.x;
-    if (j < nb) {
-      const int jm = j & (Ns - 1);
+    for (int r = 0; r < R; ++r) v[r] = a[j + r * nb];
+    if (jm > 0) {
+      double2 w[R];
+      stage_twiddles<R>(w, tw, (long long)jm * (n / (Ns * R)) * tws, inverse);
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[q][r] = a[j + r * nb];
-      if (jm > 0) {
-        double2 w[R];
-        stage_twiddles<R>(w, tw, (long long)jm * (n / (Ns * R)) * tws, inverse);
-#pragma unroll
-        for (int r = 1; r < R; ++r) v[q][r] = c_mul(v[q][r], w[r]);
-      }
-      dft_r<R>(v[q], inverse);
+      for (int r = 1; r < R; ++r) v[r] = c_mul(v[r], w[r]);
     }
+    dft_r<R>(v, inverse);
   }
   __syncthreads();
+  if (j < nb) {
+    const int idx = (j / Ns) * Ns * R + jm;
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const int j = threadIdx.x + q * blockDim.x;
-    if (j < nb) {
-      const int idx = (j / Ns) * Ns * R + (j & (Ns - 1));
-#pragma unroll
-      for (int r = 0; r < R; ++r) a[idx + r * Ns] = v[q][r];
-    }
+    for (int r = 0; r < R; ++r) a[idx + r * Ns] = v[r];
   }
   __syncthreads();
 }
 
+// Threads lds_fft needs for n points: its stages are of radix 8 but for a last
+// one of what is left (2 or 4), which has the most butterflies.
+__host__ __device__ constexpr int lds_fft_threads(int n) {
+  int rest = n;
+  while (rest % 8 == 0) rest /= 8;
+  return n / (rest > 1 ? rest : 8);
+}
+static_assert(lds_fft_threads(4096) <= kRowThreads && lds_fft_threads(2048) <= kRowThreads &&
+              lds_fft_threads(1024) <= kRowThreads, "a row of 8192 samples or fewer has one butterfly per thread");
+
 // Stockham FFT of n <= 4096 points (a power of two) in LDS buffer a, natural
 // order in and out, in radix-8 stages (a last radix-4 or -2 stage when log2 n
-// is not a multiple of 3).  Every thread of the kRowThreads takes part.
+// is not a multiple of 3).  Every thread of the workgroup takes part, at least
+// lds_fft_threads(n) of them.
 __device__ void lds_fft(double2 *a, int n, const double2 *__restrict__ tw, int tws, bool inverse) {
   for (int Ns = 1; Ns < n;) {
     const int rem = n / Ns;
@@ -199,8 +200,8 @@ __device__ void lds_fft(double2 *a, int n, const double2 *__restrict__ tw, int t
 // One row per workgroup (blockIdx.x), one input per blockIdx.y: the half
 // spectrum X[0 .. M2] of the real row x (zero beyond `cols`, and beyond the
 // `total` values an input holds from its first row on), written with zero
-// padding up to F2p.  LDS: M2 complex values.  At least M2 / 8 threads where M2
-// is a power of 8, else kRowThreads.
+// padding up to F2p.  LDS: M2 complex values.  At least lds_fft_threads(M2)
+// threads.
 template <class Rin>
 __global__ __launch_bounds__(kRowThreads) void fft_rows_r2c(FftGeom f, const Rin *__restrict__ x, long long xb, int xp,
                                                     int cols, long long total, const double2 *__restrict__ tw2,
