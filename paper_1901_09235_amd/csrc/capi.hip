@@ -494,7 +494,15 @@ int fft1_prepare(DeviceState *ds, hipStream_t stream, const Geom &g, const Fft1G
   for (const auto &s : slots) {
     const int rc = ws_get(ds, stream, s.name, s.bytes, s.p);
     if (rc == DCDL_ENOMEM) {
+      // what was obtained goes back: the other path of this call needs room too
+      HIPCK(hipStreamSynchronize(stream));
+      for (const auto &got : slots) {
+        Buf &q = ds->bufs[got.name];
+        if (q.p) HIPCK(hipFree(q.p));
+        q = Buf();
+      }
       g_err.clear();
+      ctx->dhat1 = nullptr;
       *fits = false;
       return DCDL_OK;
     }
