@@ -73,8 +73,8 @@ def parse():
     ap.add_argument("--rate", type=float, default=200.0, help="Poisson arrival rate of the serving workload")
     ap.add_argument("--rates", default="", help="serving: comma-separated offered rates to sweep (e.g. 200,600,1200)")
     ap.add_argument("--admit", type=int, default=0,
-                    help="server: workgroups of the admitted requests at most (0: one launch, -1: unbounded)")
-    ap.add_argument("--max-workers", type=int, default=0, help="server: workgroups per request at most")
+                    help="server: workers of the admitted requests at most (0: one launch, -1: unbounded)")
+    ap.add_argument("--max-workers", type=int, default=0, help="server: workers per request at most")
     ap.add_argument("--slice", type=int, default=0, help="server: rounds per launch")
     ap.add_argument("--batch-n", type=int, default=256, help="instances of the batch workload")
     ap.add_argument("--plain", type=int, default=-1,

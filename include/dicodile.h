@@ -6,8 +6,8 @@
  *
  * Problem (Sec. 2, eq. csc):  Z* = argmin_Z 1/2 ||X - Z*D||_2^2 + lambda ||Z||_1,
  * optionally with Z >= 0.  Solver: locally greedy coordinate descent (Alg. 1)
- * on a grid of workers with the soft-lock rule (Alg. 3, eq. soft_lock); one
- * worker is one GPU workgroup.
+ * on a grid of workers with the soft-lock rule (Alg. 3, eq. soft_lock); a GPU
+ * workgroup runs a team of one to four neighbouring workers.
  *
  * Conventions shared by every call (0-based, row-major, contiguous):
  *   d = 1 (signals): X (P, T),      D (K, P, L),      Z (K, T - L + 1)
@@ -125,13 +125,13 @@ typedef struct {
   int32_t tile[2];        /* sub-domain size C_m per dimension; 0 -> 2 L_i (Sec. 3) */
   int32_t grid[2];        /* worker grid W_1 x W_2; 0 -> chosen by the library: ceil(extent / tile)
                              workers per axis, each at least L long, scaled down to the
-                             workgroups that fit on the device together */
+                             workers that run on the device together (see threads) */
   int32_t warm_start;     /* 1: z_out holds the initial iterate on entry */
   int32_t refresh_every;  /* rebuild beta from its FP64 definition every this many sweeps of rounds
                              (periodic drift correction); 0 -> only after a failed final check.
                              A failed check rebuilds beta from the same FP64 contraction */
   int32_t max_polish;     /* extra solve passes after a failed final check; 0 -> 2 */
-  int32_t inner;          /* sub-domain visits per worker per round; 0 -> 1 */
+  int32_t inner;          /* sub-domain visits per worker per round, at most its sub-domains; 0 -> 1 */
   int32_t beta_prec;      /* dcdl_corr_prec of the contraction that initialises beta from X
                              (0 -> FP32: BF16X3 matrix cores; FP64: FP64 matrix cores).  Every
                              later recomputation (periodic or after a failed check) and the final
@@ -166,7 +166,8 @@ typedef struct {
   int64_t n_updates;      /* accepted coordinate updates */
   int64_t n_candidates;   /* candidates with score >= tol */
   int64_t n_softlocked;   /* candidates rejected by the soft-lock test */
-  int64_t n_rounds;       /* rounds of the busiest worker */
+  int64_t n_rounds;       /* rounds of the busiest worker, with the empty ones in which the workers
+                             learn that all have stopped */
   int64_t n_sweeps;       /* completed sweeps (every sub-domain visited once) */
   int64_t n_nonzero;      /* non-zeros of the returned Z */
   double objective;       /* FP64 F(Z) of the returned Z */
@@ -184,7 +185,9 @@ typedef struct {
   int64_t n_visits;       /* sub-domain visits (worker rounds with a sub-domain to scan) */
   int64_t n_checked;      /* positions read by soft-lock tests */
   int64_t n_patched;      /* positions of beta patched by accepted updates */
-  double t_worker_wait_s;    /* per-worker average time waiting on neighbours' progress */
+  double t_worker_wait_s;    /* per-worker average time waiting on neighbours' progress.  The four
+                                phase times are those of a workgroup's team of workers, taken in one
+                                round of sixteen and scaled to all of them */
   double t_worker_select_s;  /* ... selecting, soft-lock testing and publishing candidates */
   double t_worker_collect_s; /* ... waiting for the neighbours' candidates */
   double t_worker_apply_s;   /* ... applying accepted updates to beta, z and the move cache */
@@ -238,7 +241,7 @@ int dicodile_dtd(const dcdl_shape *shape, dcdl_dtype dtype, const void *D, void 
 int dicodile_lambda_max(const dcdl_shape *shape, dcdl_dtype dtype, const void *X, const void *D,
                         int32_t positive, double *out, void *stream);
 
-/* Solve eq. csc with LGCD + soft-lock on a grid of workgroups (Alg. 1, Alg. 3).
+/* Solve eq. csc with LGCD + soft-lock on a grid of workers (Alg. 1, Alg. 3).
  * X: (P, T...) device, opts->dtype.  D: (K, P, L...) device, opts->dtype.
  * z_out: (K, T-L+1 ...) device, opts->dtype; read first if opts->warm_start.
  * info: host, may be NULL.
@@ -377,11 +380,11 @@ int dicodile_cdl(const dcdl_shape *shape, dcdl_dtype dtype, const void *X, void 
 typedef struct {
   int32_t no_graph;     /* 1: enqueue the per-instance set-up and check kernels directly
                            instead of recording them as HIP graphs */
-  int32_t workers;      /* workgroups spread over the instances; 0 -> every co-resident slot */
+  int32_t workers;      /* workers spread over the instances; 0 -> as many as run together */
   int32_t threads;      /* as dcdl_csc_opts.threads; 0 -> 256 */
   int32_t tile[2];      /* sub-domain size; 0 -> 2 L_i (Sec. 3) */
   int32_t max_polish;   /* extra passes for instances failing the final check; 0 -> 2 */
-  int32_t inner;        /* sub-domain visits per worker per round; 0 -> 1 */
+  int32_t inner;        /* sub-domain visits per worker per round, at most its sub-domains; 0 -> 1 */
   int32_t reserved;
 } dcdl_batch_opts;
 
@@ -392,7 +395,7 @@ typedef struct {
   double t_rounds_s;    /* the persistent round launch(es) */
   double t_check_s;     /* FP64 checks and output transposes */
   int64_t n_updates;    /* summed over instances */
-  int64_t workers;      /* workgroups of the first launch */
+  int64_t workers;      /* workers of the first launch */
   int32_t n_converged;  /* instances that passed the sweep certificate and the KKT target */
   int32_t n_passes;     /* launches of the round kernel */
   int32_t used_graph;   /* 1 if the set-up and check passes ran as HIP graphs */
@@ -400,7 +403,7 @@ typedef struct {
 } dcdl_batch_info;
 
 /* Solve n independent instances of eq. csc that share the dictionary D, in one
- * persistent launch of the round kernel whose workgroups are spread over the
+ * persistent launch of the round kernel whose workers are spread over the
  * instances (each instance runs its own worker grid, soft-lock rounds and
  * stopping consensus, Alg. 3).  All shapes share ndim, P, K and L; only T
  * differs.  X and z_out are host arrays of n device pointers; D is one device
@@ -423,7 +426,7 @@ typedef struct {
   double t_tune_s;      /* wall time of the call */
   double trial_budget_s;/* round-launch time budget of one trial */
   double obj_default;   /* summed FP64 objective of the sample after one trial budget with tile
-                           2 L, 256 threads and every co-resident workgroup (mean of two runs) */
+                           2 L, 256 threads and every co-resident worker (mean of two runs) */
   double obj_best;      /* ... with the chosen configuration (<= obj_default); a configuration
                            other than the default is chosen only when it is lower by more than
                            3 obj_spread */
@@ -438,8 +441,9 @@ typedef struct {
  * sampled instance gets the worker grid it gets in the whole batch), each for
  * the same short time budget, and keeps the one whose sample reaches the
  * lowest summed FP64 objective (the most progress in equal time):
- * sub-domain tiles of 1.5, 2, 3 and 4 L_i, then 128 vs 256 threads per
- * worker, then the whole vs half the co-resident budget (fewer, larger
+ * sub-domain tiles of 1.5, 2, 3 and 4 L_i, then 128 vs 256 threads (in FP64
+ * four workers per CU vs three; in FP32 both are four and 256 stays), then the
+ * whole vs half the co-resident budget (fewer, larger
  * workers per instance).  Writes the winner into *best (the other fields of
  * *base are kept; base may be NULL).  Arguments as dicodile_csc_batch, without
  * outputs: the sample's solutions go to a library workspace.  Results are
@@ -470,16 +474,20 @@ typedef struct dcdl_server dcdl_server;
 typedef struct {
   int64_t hbm_budget_bytes; /* device memory reserved for the working sets of admitted requests
                                (beta, z, move cache: about 2 K s + 8 bytes per position, s the
-                               element size); 0 -> half of the free device memory */
+                               element size); 0 -> half of the free device memory.  Beside it a
+                               server holds the dictionary's tables, an FP64 residual of max_len
+                               positions and, for signals whose checks run by FFT, that FFT's
+                               workspace: the atoms' spectra and up to 1 GiB (without the memory
+                               for it the checks run on the matrix cores) */
   int64_t max_len;          /* positions T (d = 1) or T1*T2 (d = 2) of the largest request; sizes
                                the shared FP64 residual of the checks; 0 -> 2^20 */
-  int32_t max_workers;      /* workgroups of one request at most; 0 -> 128 */
+  int32_t max_workers;      /* workers of one request at most; 0 -> 128 */
   int32_t slice_rounds;     /* rounds per launch between admissions; 0 -> 64 */
   int32_t max_active;       /* admitted requests at most; 0 -> 256 */
   int32_t threads;          /* as dcdl_csc_opts.threads (64, 128, 192, 256); 0 -> 256 */
   int32_t tile[2];          /* sub-domain size; 0 -> 2 L_i (d = 1: tile[0] is the length) */
   int32_t max_polish;       /* extra passes for requests failing the final check; 0 -> 2 */
-  int32_t admit_workers;    /* admission stops while the admitted requests' workgroups would exceed
+  int32_t admit_workers;    /* admission stops while the admitted requests' workers would exceed
                                this (the first request is always admitted); 0 -> the co-resident
                                capacity of one launch, so the admitted set advances together in
                                one launch; -1 -> no bound (only lanes and memory limit admission).
@@ -493,7 +501,7 @@ typedef struct {
   int64_t n_launches;       /* launches of the round kernel */
   int64_t peak_active;      /* most requests admitted at once */
   int64_t peak_bytes;       /* most HBM budget in use at once */
-  int64_t peak_workers;     /* most workgroups in one launch */
+  int64_t peak_workers;     /* most workers in one launch */
   double t_rounds_s;        /* summed duration of the round launches (HIP events) */
   double t_busy_s;          /* host time with at least one admitted request */
 } dcdl_server_stats;

@@ -959,7 +959,7 @@ int residual64_async(hipStream_t stream, const Geom &g, const R *X, const double
     const long long nx = (long long)g.P * g.T1 * g.T2, HW = (long long)g.H * g.W;
     const int chunk = (int)std::max(1ll, std::min(64ll, HW / 1024));  // about 256 workgroups on small images
     hipLaunchKernelGGL((convert_kernel<R, double>), dim3(grid_stride_blocks(nx)), dim3(256), 0, stream, nx, X, res);
-    hipLaunchKernelGGL(residual_scatter<R>, dim3((unsigned)std::min<long long>((HW + 4 * chunk - 1) / (4 * chunk), 4096)),
+    hipLaunchKernelGGL(residual_atomics<R>, dim3((unsigned)std::min<long long>((HW + 4 * chunk - 1) / (4 * chunk), 4096)),
                        dim3(256), 0, stream, g, chunk, zpm, meta, D64, res, sums);
     hipLaunchKernelGGL(sum_squares, dim3(grid_stride_blocks(nx)), dim3(256), 0, stream, nx, res, sums);
   } else if (g.T1 == 1) {
@@ -1221,9 +1221,11 @@ int patch_lanes_of(const Geom &g, int vec) {
 // threads beat four workgroups of 256 (1024^2 image: 40.6 against 42.3 us).
 // Where a patch keeps no more than five waves busy (signals of few atoms), or
 // teams of four workers would not fit (uneven or many instances, whose largest
-// one would set the time), one worker per workgroup of 256
-// threads, four per CU (FP64 signal, 39 workers: 9.9 us against 10.1 with
-// 1024 threads, 10.6 and 11.1 with two and four workers per team).
+// one would set the time), one worker per workgroup of 256 threads, four per CU.
+// Signals, us per round in 256 / 1024 threads: 127 lanes 8.1 / 8.2, 254 lanes 8.25
+// / 8.4, 382 lanes (FP64) 9.5 / 8.8, 508 lanes 9.15 / 8.4.  (Small patches of more
+// than one worker per CU gain from teams as well: image of 300^2, 49 lanes, 1024
+// workers 12.7 / 9.8.)
 int plan_teams(const std::vector<std::pair<int, int>> &grids, int lanes, int cus, std::vector<Teams> *out) {
   const int n = (int)grids.size();
   out->resize(n);
@@ -1321,6 +1323,10 @@ void set_teams(Inst<R> *I, const Teams &t) {
   I->TW1 = t.TW1;
   I->TW2 = t.TW2;
   I->lane_sh = lane_map(I->KS / Vec<R>::N).sh;
+  // twice a patch of up to 1024 positions; the pass over a box addresses the
+  // apply table with 32-bit byte offsets
+  const long long u = (long long)I->U1 * I->U2;
+  I->box_share = u <= 1024 && I->K * u * I->KS * (long long)sizeof(R) < (1ll << 31) ? (int)(2 * u) : 0;
 }
 
 double now_s() {

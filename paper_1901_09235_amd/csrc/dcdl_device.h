@@ -70,6 +70,7 @@ template <class R> struct Inst {
   // G1 x G2 workers (fewer at the far edges)
   int G1, G2, TW1, TW2;
   int lane_sh;  // lane_map(KS / vector).sh
+  int box_share;   // area per update of a box that a round's updates are patched in together (0: never)
   int inner;  // sub-domain visits per round (at most Mw); 0 -> 1
   int positive, certify, soft_lock;
   int strategy;  // dcdl_select: 0 LGCD, 1 greedy, 2 cyclic (both through tile1/tile2), 3 random
@@ -1093,11 +1094,8 @@ __device__ __forceinline__ void collect(CInst<R> *I, TeamSmem<R, NT> &sm, int r,
   // empty (signal of 60,000 samples, 32 atoms of 64 taps, sub-domains of 4000:
   // 9.2 us per round in one pass over any box, 7.9 so; 800^2 image, 16 atoms of
   // 10x10, sub-domains of 100^2: 15.3 and 12.2; at four times the area 13.3).
-  // Large patches (over 1024 positions) are bandwidth-bound and go one by
-  // one.  (The pass addresses the apply table with 32-bit byte offsets.)
-  const bool un = nu > 1 && (long long)I->U1 * I->U2 <= 1024 &&
-                  (long long)(x2 - x1) * (y2 - y1) <= 2ll * nu * I->U1 * I->U2 &&
-                  (long long)I->K * I->U1 * I->U2 * I->KS * (long long)sizeof(R) < (1ll << 31);
+  // Large patches (over 1024 positions) are bandwidth-bound and go one by one.
+  const bool un = nu > 1 && (float)(x2 - x1) * (float)(y2 - y1) <= (float)(nu * I->box_share);
   if (lane < nu && !un) {
     unsigned ov = 0;
     const UCand<R> &u = sm.uc[lane];

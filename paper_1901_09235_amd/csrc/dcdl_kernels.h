@@ -483,7 +483,7 @@ __global__ __launch_bounds__(256) void sum_squares(long long n, const double *__
 // at a time as fit, from the counts (z is read only where they are not 0), and
 // each thread adds their atoms to its NA outputs: in registers, rows of an
 // atom read in contiguous runs, a row of the tile that an atom misses skipped
-// by the whole wave.  The scatter (residual_scatter) converts X, adds every atom
+// by the whole wave.  The scatter (residual_atomics) converts X, adds every atom
 // with FP64 atomics, 80 to 120 values per ns, and sums the squares in a pass of
 // its own (1024^2 image, 16x16 atoms, 248,000 non-zeros: 777 us).  The outputs
 // are summed in the order of the positions, so the residual repeats bit for
@@ -651,7 +651,7 @@ __global__ __launch_bounds__(256) void residual_gather(Geom g, const R *__restri
 // copy with FP64 atomics.  sums[2] += sum |z| and sums[3] += the number of
 // non-zeros.
 template <class R>
-__global__ __launch_bounds__(256) void residual_scatter(Geom g, int chunk, const R *__restrict__ z,
+__global__ __launch_bounds__(256) void residual_atomics(Geom g, int chunk, const R *__restrict__ z,
                                                         const uint32_t *__restrict__ meta,
                                                         const double *__restrict__ D, double *__restrict__ res,
                                                         double *__restrict__ sums) {
