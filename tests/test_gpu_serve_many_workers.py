@@ -73,3 +73,20 @@ def test_many_requests_of_a_few_workers(lib):
            for i in range(150)]
     _, grids = serve(lib, pbs, D, torch.float32, 1e-5, tile=320, slice_rounds=16)
     assert all(g == (1, 5) for g in grids)
+
+
+def test_a_request_of_too_many_teams_is_not_passed_over(lib):
+    """The oldest request makes 264 teams of four, the younger ones 256 each, which
+    hold more workers: the oldest still goes first."""
+    D = synth.gaussian_dictionary(np.random.Generator(np.random.PCG64(24)), 4, 1, (10, 10))
+    pbs = [synth.make_problem(f"i{i}", 2400 + i, P=1, T=t, K=4, L=(10, 10), rho=0.004, amp="uniform", sigma=0.1, D=D)
+           for i, t in enumerate([(324, 344)] + 5 * [(334, 334)])]
+    Xs, Dd = [dev(pb.X, torch.float32) for pb in pbs], dev(D, torch.float32)
+    lams = [0.05 * lib.dicodile_lambda_max(X, Dd) for X in Xs]
+    torch.cuda.synchronize()
+    with lib.Server(Dd, max_workers=1024, tile=(10, 10), max_len=1 << 17, admit_workers=-1, slice_rounds=16) as srv:
+        tickets = [srv.submit(X, lam, 1e-5 * lam, timeout_s=60) for X, lam in zip(Xs, lams)]
+        infos = [srv.wait(t, timeout_s=120)[1] for t in tickets]
+    assert [i["grid"] for i in infos] == [(31, 33)] + 5 * [(32, 32)]
+    assert all(i["status"] == "OK" for i in infos)
+    assert infos[0]["t_total_s"] < min(i["t_total_s"] for i in infos[1:])
