@@ -1226,6 +1226,7 @@ int patch_lanes_of(const Geom &g, int vec) {
 // / 8.4, 382 lanes (FP64) 9.5 / 8.8, 508 lanes 9.15 / 8.4.  (Small patches of more
 // than one worker per CU gain from teams as well: image of 300^2, 49 lanes, 1024
 // workers 12.7 / 9.8.)
+constexpr int kSmallPatch = 320;
 int plan_teams(const std::vector<std::pair<int, int>> &grids, int lanes, int cus, std::vector<Teams> *out) {
   const int n = (int)grids.size();
   out->resize(n);
@@ -1234,7 +1235,7 @@ int plan_teams(const std::vector<std::pair<int, int>> &grids, int lanes, int cus
     (*out)[i].set(grids[i].first, grids[i].second, 1, 1);
     workers += (*out)[i].count();
   }
-  if (lanes <= 320 && workers <= 4ll * cus) return 256;
+  if (lanes <= kSmallPatch && workers <= 4ll * cus) return 256;
   for (int per = 1; per <= 4; ++per) {
     long long wgs = 0;
     for (int i = 0; i < n; ++i) wgs += teams_of(grids[i].first, grids[i].second, per).count();

