@@ -1219,13 +1219,15 @@ int patch_lanes_of(const Geom &g, int vec) {
 // leave CUs idle (150x203 image, 48 workers, us per round: 13.2 with one per
 // team, 15.2 with two, 19.6 with four), and four workers in a team of 1024
 // threads beat four workgroups of 256 (1024^2 image: 40.6 against 42.3 us).
-// Where a patch keeps no more than five waves busy (signals of few atoms), or
-// teams of four workers would not fit (uneven or many instances, whose largest
-// one would set the time), one worker per workgroup of 256 threads, four per CU.
-// Signals, us per round in 256 / 1024 threads: 127 lanes 8.1 / 8.2, 254 lanes 8.25
-// / 8.4, 382 lanes (FP64) 9.5 / 8.8, 508 lanes 9.15 / 8.4.  (Small patches of more
-// than one worker per CU gain from teams as well: image of 300^2, 49 lanes, 1024
-// workers 12.7 / 9.8.)
+// At most two workers per CU of patches that keep no more than five waves busy
+// (signals of few atoms), and instances whose workers do not fit in teams of four
+// (uneven or many, whose largest one would set the time), run one worker per
+// workgroup of 256 threads, up to four per CU.  Signals, us per round in 256 /
+// 1024 threads: 127 lanes 8.1 / 8.2, 254 lanes 8.25 / 8.4, 382 lanes (FP64) 9.5 /
+// 8.8, 508 lanes 9.15 / 8.4.  More workers of small patches: signal, 94 lanes,
+// 1024 workers 7.45 / 7.0; image of 300^2, 49 lanes, 1024 workers 12.7 / 9.8; and
+// a launch of 256-thread workgroups that needs more than two slots per CU may
+// wait for ever beside another stream's kernels (server_loop has the reason).
 constexpr int kSmallPatch = 320;
 int plan_teams(const std::vector<std::pair<int, int>> &grids, int lanes, int cus, std::vector<Teams> *out) {
   const int n = (int)grids.size();
@@ -1235,7 +1237,7 @@ int plan_teams(const std::vector<std::pair<int, int>> &grids, int lanes, int cus
     (*out)[i].set(grids[i].first, grids[i].second, 1, 1);
     workers += (*out)[i].count();
   }
-  if (lanes <= kSmallPatch && workers <= 4ll * cus) return 256;
+  if (lanes <= kSmallPatch && workers <= 2ll * cus) return 256;
   for (int per = 1; per <= 4; ++per) {
     long long wgs = 0;
     for (int i = 0; i < n; ++i) wgs += teams_of(grids[i].first, grids[i].second, per).count();
